@@ -606,38 +606,31 @@ VALU_PEAK_T = 256 * 128 * 2.4e9 / 1e12
 # Issue rates of the instructions of the GEMM kernels' k-loops, lanes per
 # clock per CU at 2.4 GHz, measured by bench.py --ceilings (chains of one
 # instruction, profiles/ceilings_patterns_and_valu.txt): two-operand adds,
-# multiplies and ands issue at about 112-120; v_bfe_u32, v_add3_u32,
-# v_rndne_f32 and the packed half-precision v_pk_add_f16 / v_pk_mul_f16
-# (two lanes of work each) at about 62.
+# multiplies, ands and the fma issue at about 112-120; v_rndne_f32, the
+# conversion to bfloat16 and the packed half-precision forms (two lanes of
+# work each) at about 62.
 VALU_RATES = {"v_and_b32": 119.3, "v_add_f32": 112.7, "v_sub_f32": 118.5, "v_mul_f32": 116.6,
-              "v_bfe_u32": 62.1, "v_add3_u32": 62.2, "v_rndne_f32": 62.7,
-              "v_pk_add_f16": 62.2, "v_pk_mul_f16": 62.0, "v_cvt_pk_bf16_f32": 62.2,
-              "v_lshlrev_b32": 115.0}  # the shift not probed: the two-operand forms' rate
+              "v_fma_f32": 118.2, "v_rndne_f32": 62.7, "v_pk_add_f16": 62.2, "v_cvt_pk_bf16_f32": 62.2,
+              "v_pk_fma_f16": 62.0}  # the packed fma not probed: the packed multiply's rate
 # VALU instructions per multiply-accumulate of each k-loop, counted in the
-# kernels' ISA (one loop iteration: 16 k-steps of the thread's 4 x 4 outputs).
-#   k_lp_gemm_h (the accumulator is IEEE half): a packed multiply and a packed
-#     add per two outputs; Kahan four packed adds.  The loop also issues 16
-#     ds_read2_b64 (the operands from LDS).
+# kernels' ISA.
+#   k_lp_gemm_h (the accumulator is IEEE half): one packed fma per two outputs
+#     in the k-steps whose products are all halves (88 % of them on this
+#     shape; the others a packed multiply and a packed add); Kahan three packed
+#     adds more.
 #   k_lp_gemm, products on the accumulator's subnormal grid (1-5-2 inputs into
 #     1-5-7): the product, its rint, the multiply into the working domain, the
-#     add and its rounding (v_bfe_u32, v_add3_u32, v_and_b32); Kahan rounds four
-#     adds.  The loop also issues 32 ds_read_b128.
-#   k_lp_gemm, exact products into bfloat16 (1-5-2 inputs into 1-8-7: every
-#     product fits and none is subnormal): the product, the add, and its
-#     rounding by a packed conversion to bfloat16 for two chains
-#     (v_cvt_pk_bf16_f32) and the two halves taken back (v_lshlrev_b32,
-#     v_and_b32); Kahan rounds four adds so.
+#     add and its rounding by the conversion to bfloat16; Kahan rounds four
+#     adds.
+#   k_lp_gemm, exact products into bfloat16 (1-5-2 inputs into 1-8-7): one fma
+#     and the conversion; Kahan rounds four adds so.
 GEMM_LOOP_MIX = {
-    "sequential": {"v_pk_mul_f16": 0.5, "v_pk_add_f16": 0.5},
-    "kahan": {"v_pk_mul_f16": 0.5, "v_pk_add_f16": 2.0},
-    "sequential_emulated": {"v_mul_f32": 2, "v_rndne_f32": 1, "v_add_f32": 1, "v_and_b32": 1, "v_bfe_u32": 1,
-                            "v_add3_u32": 1},
-    "kahan_emulated": {"v_mul_f32": 2, "v_rndne_f32": 1, "v_add_f32": 1, "v_sub_f32": 3, "v_and_b32": 4,
-                       "v_bfe_u32": 4, "v_add3_u32": 4},
-    "sequential_bf16": {"v_mul_f32": 1, "v_add_f32": 1, "v_cvt_pk_bf16_f32": 0.5, "v_lshlrev_b32": 0.5,
-                        "v_and_b32": 0.5},
-    "kahan_bf16": {"v_mul_f32": 1, "v_add_f32": 1, "v_sub_f32": 3, "v_cvt_pk_bf16_f32": 2, "v_lshlrev_b32": 2,
-                   "v_and_b32": 2},
+    "sequential": {"v_pk_fma_f16": 0.5},
+    "kahan": {"v_pk_fma_f16": 0.5, "v_pk_add_f16": 1.5},
+    "sequential_emulated": {"v_mul_f32": 2, "v_rndne_f32": 1, "v_add_f32": 1, "v_cvt_pk_bf16_f32": 1},
+    "kahan_emulated": {"v_mul_f32": 2, "v_rndne_f32": 1, "v_add_f32": 1, "v_sub_f32": 3, "v_cvt_pk_bf16_f32": 4},
+    "sequential_bf16": {"v_fma_f32": 1, "v_cvt_pk_bf16_f32": 1},
+    "kahan_bf16": {"v_fma_f32": 1, "v_add_f32": 1, "v_sub_f32": 2, "v_cvt_pk_bf16_f32": 4},
 }
 GEMM_SHAPE = (4096, 1024, 4096)  # BERT-large FFN up-projection at 8 x 512 tokens: M, K, N
 

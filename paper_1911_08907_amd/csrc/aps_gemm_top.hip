@@ -1,0 +1,13 @@
+// aps_gemm_top.hip -- low-precision GEMM: accumulators of class TOP.
+#include "aps_gemm.hpp"
+
+namespace aps {
+
+void launch_gemm_top(int variant, int pm, bool kahan, hipStream_t s, const GemmArgs& g, const FmtK& fi,
+                     const FmtK& fa) {
+    if (variant == V_TOP_F32) launch_gemm_v<V_TOP_F32>(pm, kahan, s, g, fi, fa);
+    if (variant == V_TOP_F64) launch_gemm_v<V_TOP_F64>(pm, kahan, s, g, fi, fa);
+    if (variant == V_TOP_M0) launch_gemm_v<V_TOP_M0>(pm, kahan, s, g, fi, fa);
+}
+
+}  // namespace aps

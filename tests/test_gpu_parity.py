@@ -874,3 +874,75 @@ def test_kahan_compensation_nan_does_not_reach_the_sum(dev, f):
     got = A.aps_lp_gemm(torch.from_numpy(Am).to(dev), torch.from_numpy(Bm).to(dev), fin, f, A.APS_ACC_KAHAN)
     torch.cuda.synchronize()
     assert np.isinf(refg).all() and same_f32(got.cpu().numpy(), refg)
+
+
+# (input, accumulator) pairs whose products need no rounding, so that multiply
+# and add fuse, and their neighbours that keep the two apart
+GEMM_FUSED_PAIRS = [
+    (F(4, 3), F(5, 10)),        # half: every product of two inputs is a half
+    (F(5, 2), F(5, 10)),        # half: tested per k-step
+    (F(5, 2, 16), F(5, 10)),    # half, the general input cast: two instructions
+    (F(4, 3), F(5, 7)),         # 7 mantissa bits: products reach the subnormal range but lie on its grid
+    (F(5, 2), F(5, 7)),         # 7 mantissa bits, products rounded on the grid
+    (F(3, 1), F(3, 7)),         # the same, LOW class
+    (F(3, 1, -2), F(4, 7)),     # products fit but overflow the accumulator: not fused
+    (F(3, 1, -6), F(5, 9)),    # the same, accumulator of 9 mantissa bits
+    (F(4, 3), F(5, 9)),         # fused, TOP class
+    (F(4, 3), F(8, 23)),        # fused, fp32 accumulator
+    (F(4, 3), F(6, 12)),        # adds in fp64: not fused
+]
+
+
+@pytest.mark.parametrize("acc", [A.APS_ACC_SEQUENTIAL, A.APS_ACC_KAHAN])
+@pytest.mark.parametrize("fin,facc", GEMM_FUSED_PAIRS, ids=lambda f: str(f))
+def test_lp_gemm_fused_products_and_small_tiles(dev, fin, facc, acc):
+    # K around the staged k-tiles (16, 32, 64) and the runs of 8 steps after
+    # them; M and N around the tiles of 16 and 32; N = 1 and 3 are narrower
+    # than a 16-byte load of B; A, B and C start at odd elements
+    rng = np.random.default_rng(1200 + 7 * fin.e + facc.m + 31 * acc)
+    for M, N, K in [(1, 3, 130), (17, 1, 33), (16, 16, 64), (33, 31, 65), (31, 130, 79), (15, 17, 15), (40, 64, 32),
+                    (2, 5, 16), (65, 48, 72)]:
+        for specials in (False, True):
+            Am, Bm = _gemm_inputs(rng, M, N, K, fin, specials)
+            log(f"lp_gemm fused {fin}->{facc} acc={acc} M={M} N={N} K={K} specials={specials}")
+            a = torch.full((M * (K + 1) + 1,), float("nan"), device=dev)[1:].view(M, K + 1)[:, :K]
+            b = torch.full((K * (N + 2) + 1,), float("nan"), device=dev)[1:].view(K, N + 2)[:, :N]
+            c = torch.full((M * (N + 1) + 1,), 7.0, device=dev)[1:].view(M, N + 1)[:, :N]
+            a.copy_(torch.from_numpy(Am))
+            b.copy_(torch.from_numpy(Bm))
+            A.aps_lp_gemm(a, b, fin, facc, acc, C=c)
+            torch.cuda.synchronize()
+            ref = O.lp_gemm(Am, Bm, ofmt(fin), ofmt(facc), acc)
+            g = c.cpu().numpy()
+            assert same_f32(g, ref), (fin, facc, acc, M, N, K, specials, first_diff(g, ref))
+            assert bool((c.as_strided((M, 1), (N + 1, 1), c.storage_offset() + N) == 7.0).all())
+
+
+@pytest.mark.parametrize("M,N,fin,facc,acc", [
+    (3585, 3455, F(5, 2), F(5, 10), 0),   # half, 8 x 8 outputs per thread
+    (2047, 1930, F(5, 2), F(5, 10), 0),   # 8 x 4
+    (1930, 2047, F(4, 3), F(5, 10), 1),   # 8 x 4, Kahan
+    (1025, 1023, F(5, 2), F(5, 10), 0),   # 4 x 4
+    (1030, 2050, F(5, 2), F(8, 23), 0),   # fp32 accumulator, 4 x 4
+    (897, 895, F(4, 3), F(8, 7), 0),      # 2 x 2
+    (401, 193, F(5, 2), F(5, 7), 0),      # 1 x 2
+])
+def test_lp_gemm_large_tiles_sampled(dev, M, N, fin, facc, acc):
+    # ragged outputs that fill the chip with each tile; magnitudes such that
+    # some k-steps' products are exact in half and some are not; rows and
+    # columns at the tiles' edges against the oracle
+    rng = np.random.default_rng(1300 + M % 11)
+    K = 41
+    Am = (rng.standard_normal((M, K)) * 2.0 ** rng.uniform(-9, 2, (1, K))).astype(np.float32)
+    Bm = (rng.standard_normal((K, N)) * 2.0 ** rng.uniform(-9, 2, (K, 1))).astype(np.float32)
+    Am[5, 7], Bm[9, 11], Am[M - 1, 3], Bm[20, N - 1] = np.inf, -np.inf, np.nan, 3e38
+    log(f"lp_gemm large tiles M={M} N={N} {fin}->{facc} acc={acc}")
+    got = A.aps_lp_gemm(torch.from_numpy(Am).to(dev), torch.from_numpy(Bm).to(dev), fin, facc, acc)
+    torch.cuda.synchronize()
+    g = got.cpu().numpy()
+    rows = np.unique(np.clip([0, 1, 5, 31, 32, 63, 64, 127, 128, 130, M // 2, M - 129, M - 2, M - 1], 0, M - 1))
+    cols = np.unique(np.clip([0, 3, 11, 63, 64, 127, 128, N // 2, N - 65, N - 4, N - 1], 0, N - 1))
+    ref_r = O.lp_gemm(Am[rows], Bm, ofmt(fin), ofmt(facc), acc)
+    assert same_f32(g[rows], ref_r), first_diff(g[rows], ref_r)
+    ref_c = O.lp_gemm(Am, np.ascontiguousarray(Bm[:, cols]), ofmt(fin), ofmt(facc), acc)
+    assert same_f32(np.ascontiguousarray(g[:, cols]), ref_c), first_diff(g[:, cols], ref_c)
