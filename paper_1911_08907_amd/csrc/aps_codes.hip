@@ -27,6 +27,17 @@ __device__ __forceinline__ void elem_scales_n(const Layers& ly, const ChunkInfo&
     }
 }
 
+// Rows per register set.  A thread's sums and decoded codes take 32 (nibbles:
+// 64) registers, so two sets of 4 rows leave two waves per SIMD where sets
+// of 2 leave four (ResNet-50, W = 8, sum and decode: 1-3-0 183 -> 121 us,
+// 1-4-3 94 -> 89, 1-5-2 79 -> 78; W = 256 the same).
+constexpr int CODES_UNROLL = 2;
+
+// The hardware form a palette entry's codes of class CC take.
+__host__ __device__ __forceinline__ int hw_of_codes(const FmtK& f, int cc) {
+    return cc == 1 && (f.hw == HW_E5M2 || f.hw == HW_E4M3) ? f.hw : (cc == 2 && f.hw == HW_HALF ? f.hw : HW_NONE);
+}
+
 // Code e (0..EPT-1) of a thread's 16-byte slice.
 template <int CC>
 __device__ __forceinline__ uint32_t slice_code(const f4& v, int e) {
@@ -39,13 +50,25 @@ __device__ __forceinline__ uint32_t slice_code(const f4& v, int e) {
 // The W-worker rounded sum of already scaled and cast gradients given as
 // packed codes (the low-precision values the workers exchange).  A thread
 // owns the codes in 16 bytes of each row: 32 nibble, 16 byte or 8 uint16
-// codes.  Codes of up to 8 bits decode through a table of working-domain
-// values in LDS; 16-bit codes decode arithmetically.
-template <int V, int CC>
+// codes.  Three formats run on the hardware's conversions (HW):
+//   1-5-2   decoded two codes per instruction and every sum rounded by the
+//           conversion to E5M2 and back (native values): 2.5 VALU
+//           instructions per code;
+//   1-4-3   decoded by the conversion from E4M3 and a multiply into the
+//           working domain, where overflow is fp32's;
+//   1-5-10  the codes are halves: one packed half add per two codes.
+// Other codes of up to 8 bits decode through a table of working-domain values
+// in LDS, whose random reads (about 7 clocks per wave and code with bank
+// conflicts) weigh as much as the HBM reads; other 16-bit codes decode
+// arithmetically.  ResNet-50, W = 8, the sum to codes and their decode: 1-5-2
+// 104 -> 75 us, 1-4-3 107 -> 85, 1-5-10 367 -> 112; W = 256 1-5-2 1197 -> 1069.
+template <int V, int CC, int HW>
 __global__ __launch_bounds__(BLOCK) void k_sim_reduce_codes(CodesArgs a, Layers ly, Pal pal) {
     constexpr int EPT = CC == 0 ? 32 : (CC == 1 ? 16 : 8);
     constexpr int64_t CHC = (int64_t)BLOCK * EPT;
-    __shared__ float lut[256];
+    constexpr bool TABLE = CC < 2 && HW == HW_NONE;
+    constexpr bool NATIVE = HW == HW_E5M2 || HW == HW_HALF;  // s holds native values, not working-domain ones
+    __shared__ float lut[TABLE ? 256 : 1];
     // each wave's fp32 outputs pass through its own LDS slots, so that they
     // leave in stores of consecutive 16-byte pieces per lane (a lane's EPT
     // outputs written as EPT/4 stores 4*EPT bytes apart wrote up to 1.7x
@@ -63,8 +86,8 @@ __global__ __launch_bounds__(BLOCK) void k_sim_reduce_codes(CodesArgs a, Layers 
         hint = ci.i0;
         if (ci.mixed) continue;
         const FmtK& f = pal.f[ci.pidx];
-        if (f.variant != V) continue;
-        if constexpr (CC < 2) {
+        if (f.variant != V || hw_of_codes(f, CC) != HW) continue;
+        if constexpr (TABLE) {
             if (ci.pidx != lut_pidx) {  // uniform
                 __syncthreads();
                 for (int t = threadIdx.x; t < (CC == 0 ? 16 : 256); t += BLOCK)
@@ -78,25 +101,55 @@ __global__ __launch_bounds__(BLOCK) void k_sim_reduce_codes(CodesArgs a, Layers 
         const uint8_t* p = a.codes + code_byte(j, CC);
         const int64_t rb = a.row_bytes;
         float s[EPT];
+        h2 sh[4];  // HW_HALF: the sums, two per register
         uint32_t bad = 0;
-        auto dec = [&](uint32_t code) -> float {
-            if constexpr (CC < 2) return lut[code];
-            else return __builtin_amdgcn_ldexpf(decode(code, f), f.k);
+        uint32_t nan[4] = {0, 0, 0, 0};  // HW_E4M3: the top bit of byte e: a code of element e was a NaN
+        // the values of a thread's codes in one row
+        auto decode_row = [&](const f4& v, float (&d)[EPT]) {
+            if constexpr (HW == HW_E5M2) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) decode4_e5m2(f2u(v[q]), d + 4 * q);
+            } else if constexpr (HW == HW_E4M3) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    decode4_e4m3(f2u(v[q]), d + 4 * q);
+                    nan[q] |= nan_bytes_e4m3(f2u(v[q]));  // a NaN stays to the chain's end
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < EPT; ++e) {
+                    const uint32_t code = slice_code<CC>(v, e);
+                    if constexpr (TABLE) d[e] = lut[code];
+                    else d[e] = __builtin_amdgcn_ldexpf(decode(code, f), f.k);
+                }
+            }
         };
-        stream_rows(
+        stream_rows<CODES_UNROLL>(
             a.W, [&](int r) { return ld4((const float*)(p + (int64_t)r * rb)); }, [&]() {},
             [&](const f4& v) {
+                if constexpr (HW == HW_HALF) {
 #pragma unroll
-                for (int e = 0; e < EPT; ++e) s[e] = dec(slice_code<CC>(v, e));
+                    for (int q = 0; q < 4; ++q) sh[q] = __builtin_bit_cast(h2, f2u(v[q]));
+                } else {
+                    decode_row(v, s);
+                }
             },
             [&](const f4& v, bool valid) {
-                if (valid) {
-                    // all of the row's table reads first, so their latencies
-                    // overlap instead of each add waiting for its own read
-                    float d[EPT];
+                if (!valid) return;
+                if constexpr (HW == HW_HALF) {
 #pragma unroll
-                    for (int e = 0; e < EPT; ++e) d[e] = dec(slice_code<CC>(v, e));
-                    if constexpr (CC < 2) __builtin_amdgcn_sched_barrier(0);
+                    for (int q = 0; q < 4; ++q) sh[q] = sh[q] + __builtin_bit_cast(h2, f2u(v[q]));  // rounded to half
+                    return;
+                }
+                // all of the row's values first, so the table reads' latencies
+                // overlap instead of each add waiting for its own read
+                float d[EPT];
+                decode_row(v, d);
+                if constexpr (TABLE) __builtin_amdgcn_sched_barrier(0);
+                if constexpr (HW == HW_E5M2) {
+#pragma unroll
+                    for (int e = 0; e < EPT; e += 2) round2_e5m2(s[e] + d[e], s[e + 1] + d[e + 1], s[e], s[e + 1]);
+                } else {
 #pragma unroll
                     for (int e = 0; e < EPT; ++e) {
                         bool b = false;
@@ -105,8 +158,18 @@ __global__ __launch_bounds__(BLOCK) void k_sim_reduce_codes(CodesArgs a, Layers 
                     }
                 }
             });
+        if constexpr (HW == HW_HALF) {
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) s[e] = (float)sh[e >> 1][e & 1];
+        }
+        if constexpr (HW == HW_E4M3) {
+#pragma unroll
+            for (int e = 0; e < EPT; ++e)
+                s[e] = (nan[e >> 2] >> (8 * (e & 3) + 7)) & 1u ? __builtin_nanf("") : s[e];
+        }
         // output exponents, per element when the chunk crosses layers
         const int32_t fdom = ((a.flags & APS_OUTPUT_SCALED) ? 0 : 1);
+        const int32_t k = NATIVE ? 0 : f.k;
         int32_t ft[EPT];
         if (ci.i0 == ci.i1) {
             const int32_t t = ly.scale_exp ? clamp_exp(cld(ly.scale_exp, ci.i0)) : 0;
@@ -120,13 +183,29 @@ __global__ __launch_bounds__(BLOCK) void k_sim_reduce_codes(CodesArgs a, Layers 
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
             const float se = VT<V>::m0 ? (((bad >> e) & 1u) ? __builtin_nanf("") : s[e]) : s[e];
-            o[e] = __builtin_amdgcn_ldexpf(se, -(fdom * ft[e] + f.k));
-            if (a.codes_out) {
-                const uint32_t cd = encode(__builtin_amdgcn_ldexpf(se, -f.k), f);
-                if constexpr (CC == 0) cw[e >> 3] |= (cd & 15u) << ((e & 7) * 4);
-                else if constexpr (CC == 1) cw[e >> 2] |= (cd & 255u) << ((e & 3) * 8);
-                else cw[e >> 1] |= (cd & 0xFFFFu) << ((e & 1) * 16);
+            o[e] = __builtin_amdgcn_ldexpf(se, -(fdom * ft[e] + k));
+            if constexpr (HW == HW_NONE) {
+                if (a.codes_out) {
+                    const uint32_t cd = encode(__builtin_amdgcn_ldexpf(se, -f.k), f);
+                    if constexpr (CC == 0) cw[e >> 3] |= (cd & 15u) << ((e & 7) * 4);
+                    else if constexpr (CC == 1) cw[e >> 2] |= (cd & 255u) << ((e & 3) * 8);
+                    else cw[e >> 1] |= (cd & 0xFFFFu) << ((e & 1) * 16);
+                }
             }
+        }
+        if (HW == HW_E5M2 && a.codes_out) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) cw[q] = encode4_e5m2(s[4 * q], s[4 * q + 1], s[4 * q + 2], s[4 * q + 3]);
+        }
+        if (HW == HW_E4M3 && a.codes_out) {
+            constexpr float ik = 0x1p-120f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                cw[q] = encode4_e4m3(s[4 * q] * ik, s[4 * q + 1] * ik, s[4 * q + 2] * ik, s[4 * q + 3] * ik);
+        }
+        if (HW == HW_HALF && a.codes_out) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) cw[q] = canonical2_half(__builtin_bit_cast(uint32_t, sh[q]));
         }
         const int lane = threadIdx.x & 63;
         const int64_t wbase = j - (int64_t)lane * EPT;  // the wave's first element
@@ -273,16 +352,29 @@ extern "C" int aps_sim_reduce_codes(const void* codes, int32_t W, int64_t ld, in
     CodesArgs a{(const uint8_t*)codes, out, (uint8_t*)codes_out, row_bytes, W, flags};
     const int64_t ept = ccls == 0 ? 32 : (ccls == 1 ? 16 : 8);
     const int64_t nchunks = (n + BLOCK * ept - 1) / (BLOCK * ept);
-    const dim3 grid((unsigned)grid_for(nchunks, BLOCKS_PER_CU));
-    const unsigned vm = variant_mask(pal, n_fmts);
-#define APS_LAUNCH_C(v)                                                                                      \
-    if (vm & (1u << (v))) {                                                                                  \
-        if (ccls == 0) hipLaunchKernelGGL((k_sim_reduce_codes<v, 0>), grid, dim3(BLOCK), 0, s, a, ly, pal);  \
-        if (ccls == 1) hipLaunchKernelGGL((k_sim_reduce_codes<v, 1>), grid, dim3(BLOCK), 0, s, a, ly, pal);  \
-        if (ccls == 2) hipLaunchKernelGGL((k_sim_reduce_codes<v, 2>), grid, dim3(BLOCK), 0, s, a, ly, pal);  \
+    // a block per chunk up to 64 per CU: blocks of a chunk or two balance
+    // better than 16 per CU (ResNet-50, W = 64: 1-5-2 334 -> 307 us, 1-5-10
+    // 639 -> 579 us; W = 8 the same)
+    const dim3 grid((unsigned)grid_for(nchunks, 64));
+    unsigned vm = 0, hm = 0;  // variants of the entries without, and forms of those with, hardware codes
+    for (int i = 0; i < n_fmts; ++i) {
+        const int hw = hw_of_codes(pal.f[i], ccls);
+        if (hw) hm |= 1u << hw;
+        else vm |= 1u << pal.f[i].variant;
+    }
+#define APS_C(v, c, h) hipLaunchKernelGGL((k_sim_reduce_codes<v, c, h>), grid, dim3(BLOCK), 0, s, a, ly, pal)
+    if (hm & (1u << HW_E5M2)) APS_C(V_TOP_F32, 1, HW_E5M2);
+    if (hm & (1u << HW_E4M3)) APS_C(V_LOW_F32, 1, HW_E4M3);
+    if (hm & (1u << HW_HALF)) APS_C(V_TOP_F32, 2, HW_HALF);
+#define APS_LAUNCH_C(v)                      \
+    if (vm & (1u << (v))) {                  \
+        if (ccls == 0) APS_C(v, 0, HW_NONE); \
+        if (ccls == 1) APS_C(v, 1, HW_NONE); \
+        if (ccls == 2) APS_C(v, 2, HW_NONE); \
     }
     APS_FOR_VARIANTS(APS_LAUNCH_C)
 #undef APS_LAUNCH_C
+#undef APS_C
     if (fmt_idx && n_fmts > 1 && L > 1) {
         if (ccls == 0) hipLaunchKernelGGL(k_sim_reduce_codes_mixed<0>, dim3((unsigned)L), dim3(BLOCK), 0, s, a, ly, pal);
         if (ccls == 1) hipLaunchKernelGGL(k_sim_reduce_codes_mixed<1>, dim3((unsigned)L), dim3(BLOCK), 0, s, a, ly, pal);

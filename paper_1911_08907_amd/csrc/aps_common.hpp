@@ -261,6 +261,74 @@ __device__ __forceinline__ float decode(uint32_t code, const FmtK& f) {
     return ((code >> (f.e + f.m)) & 1u) ? -a : a;
 }
 
+// ------------------------------------------- codes by hardware conversion
+//
+// A 1-5-2 code is the E5M2 byte of its value and a 1-5-10 code the half's
+// bits, INF included; only a NaN's code is not the hardware's (any NaN
+// pattern), and is set to the canonical one here.  A 1-4-3 code is the E4M3
+// byte up to 240; E4M3 reads 1-4-3's INF (0x78) as 256 and its NaN codes
+// 0x79..0x7E as 288..448, which times 2^120 are all INF in fp32: right for
+// INF, while a NaN code is found on its bits.
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+using h2 = _Float16 __attribute__((ext_vector_type(2)));
+
+// Four 1-5-2 codes (bytes of w) to values.
+__device__ __forceinline__ void decode4_e5m2(uint32_t w, float d[4]) {
+    const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_bf8(w, false), hi = __builtin_amdgcn_cvt_pk_f32_bf8(w, true);
+    d[0] = lo[0];
+    d[1] = lo[1];
+    d[2] = hi[0];
+    d[3] = hi[1];
+}
+
+// Four 1-4-3 codes to values times 2^120 (the working domain); NaN codes to INF.
+__device__ __forceinline__ void decode4_e4m3(uint32_t w, float d[4]) {
+    const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8(w, false), hi = __builtin_amdgcn_cvt_pk_f32_fp8(w, true);
+    constexpr float k = 0x1p120f;
+    d[0] = lo[0] * k;
+    d[1] = lo[1] * k;
+    d[2] = hi[0] * k;
+    d[3] = hi[1] * k;
+}
+
+// The top bit of each byte is set where it is a NaN code of 1-4-3 (magnitude
+// above 0x78); the other bits mean nothing.
+__device__ __forceinline__ uint32_t nan_bytes_e4m3(uint32_t w) { return (w & 0x7F7F7F7Fu) + 0x07070707u; }
+
+// The codes of four 1-4-3 values, one per byte; INF as 0x78 (E4M3's 256), NaN
+// as 0x7C.
+__device__ __forceinline__ uint32_t encode4_e4m3(float x0, float x1, float x2, float x3) {
+    const auto lim = [](float x) { return __builtin_amdgcn_fmed3f(x, -256.0f, 256.0f); };
+    const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(lim(x0), lim(x1), 0, false);
+    uint32_t c = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(lim(x2), lim(x3), lo, true);
+    c = x0 != x0 ? (c & 0xFFFFFF00u) | 0x0000007Cu : c;
+    c = x1 != x1 ? (c & 0xFFFF00FFu) | 0x00007C00u : c;
+    c = x2 != x2 ? (c & 0xFF00FFFFu) | 0x007C0000u : c;
+    return x3 != x3 ? (c & 0x00FFFFFFu) | 0x7C000000u : c;
+}
+
+// R(x) for two values of 1-5-2.
+__device__ __forceinline__ void round2_e5m2(float x0, float x1, float& r0, float& r1) {
+    const f32x2 v = __builtin_amdgcn_cvt_pk_f32_bf8(__builtin_amdgcn_cvt_pk_bf8_f32(x0, x1, 0, false), false);
+    r0 = v[0];
+    r1 = v[1];
+}
+
+// The codes of R(x) for four values of 1-5-2, one per byte; NaN as 0x7E.
+__device__ __forceinline__ uint32_t encode4_e5m2(float x0, float x1, float x2, float x3) {
+    const int lo = __builtin_amdgcn_cvt_pk_bf8_f32(x0, x1, 0, false);
+    const uint32_t c = (uint32_t)__builtin_amdgcn_cvt_pk_bf8_f32(x2, x3, lo, true);
+    const uint32_t nan = (((c & 0x7F7F7F7Fu) + 0x03030303u) >> 7) & 0x01010101u;  // above 0x7C
+    return (c | (nan << 1)) & ~nan;
+}
+
+// The codes of two halves; NaN as 0x7E00.
+__device__ __forceinline__ uint32_t canonical2_half(uint32_t c) {
+    const uint32_t nan = (((c & 0x7FFF7FFFu) + 0x03FF03FFu) >> 15) & 0x00010001u;  // above 0x7C00
+    return nan ? (c & ~(nan * 0xFFFFu)) | (nan * 0x7E00u) : c;
+}
+
 __host__ __device__ __forceinline__ int64_t code_byte(int64_t j, int cls) {
     return cls == 0 ? (j >> 1) : (cls == 1 ? j : 2 * j);
 }

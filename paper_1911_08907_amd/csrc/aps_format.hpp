@@ -69,12 +69,21 @@ enum Variant : int32_t {
     N_VARIANTS = 11
 };
 
+// Formats whose values and codes the hardware converts to and from fp32.
+enum Hw : int32_t {
+    HW_NONE = 0,
+    HW_E5M2 = 1,  // 1-5-2, bias 15: the OCP E5M2 8-bit float
+    HW_E4M3 = 2,  // 1-4-3, bias 7: the OCP E4M3 8-bit float below 248 (above, E4M3 has no INF and goes on to 448)
+    HW_HALF = 3,  // 1-5-10, bias 15: IEEE half
+};
+
 // Everything a kernel needs about one palette entry; built on the host.
 struct FmtK {
     int32_t e, m, bias, emin, emax;
     int32_t k;        // working value = native value * 2^k
     int32_t j;        // LOW: subnormal rounding happens at working * 2^-j
     int32_t variant;  // Variant
+    int32_t hw;       // Hw
     uint32_t sh;      // 23 - m: dropped fp32 mantissa bits
     uint32_t lsbw;    // width (0/1) of the tie bit read at position sh
     uint32_t half;    // increment added before the tie bit
@@ -179,6 +188,10 @@ inline FmtK make_fmtk(const aps_format& f) {
         o.variant = f.m == 0 ? V_TOP_M0 : (acc == ACC_F64 ? V_TOP_F64 : V_TOP_F32);
     else
         o.variant = f.m == 0 ? V_LOW_M0 : (acc == ACC_F64 ? V_LOW_F64 : V_LOW_F32);
+    o.hw = (f.e == 5 && f.m == 2 && f.bias == 15)    ? HW_E5M2
+           : (f.e == 4 && f.m == 3 && f.bias == 7)   ? HW_E4M3
+           : (f.e == 5 && f.m == 10 && f.bias == 15) ? HW_HALF
+                                                     : HW_NONE;
     o.code_bits = 1 + f.e + f.m;
     o.emax_code = (int32_t)(((1u << f.e) - 1u) << f.m);
     return o;

@@ -48,7 +48,6 @@ enum GemmProduct {
 // conversion issues at half the rate of the shift and the mask) in one more
 // instruction per add.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float round_b7(float x) {
     return __builtin_bit_cast(float, __builtin_convertvector(f32x2{0.0f, x}, bf16x2));
@@ -79,16 +78,8 @@ __device__ __forceinline__ float round_b7(float x) {
 // OCP E5M2 8-bit float.  The hardware's conversion of fp32 to it (round to
 // nearest even, no saturation: beyond the largest finite value the result is
 // INF, a NaN stays NaN, subnormals kept) and back to fp32 is this format's
-// cast exactly; the two agree on every fp32 bit pattern.  Two values per
-// conversion.
+// cast exactly (round2_e5m2); the two agree on every fp32 bit pattern.
 constexpr int VI_E5M2 = 100;
-
-__device__ __forceinline__ void cast_e5m2x2(float x0, float x1, float& r0, float& r1) {
-    const int pk = __builtin_amdgcn_cvt_pk_bf8_f32(x0, x1, 0, false);  // bytes 0 and 1
-    const f32x2 v = __builtin_amdgcn_cvt_pk_f32_bf8(pk, false);
-    r0 = v[0];
-    r1 = v[1];
-}
 
 // Input format 1-4-3 with bias 7 shares its layout, subnormals and rounding
 // with the OCP E4M3 8-bit float below 248; E4M3 has no INF and goes on to
@@ -106,8 +97,8 @@ __device__ __forceinline__ void cast_e4m3x2(float x0, float x1, float& r0, float
 
 // The launch's input mode: a hardware conversion, or the format's class.
 inline bool input_mode_is(int vi, const FmtK& f) {
-    if (vi == VI_E5M2) return f.e == 5 && f.m == 2 && f.bias == 15;
-    if (vi == VI_E4M3) return f.e == 4 && f.m == 3 && f.bias == 7;
+    if (vi == VI_E5M2) return f.hw == HW_E5M2;
+    if (vi == VI_E4M3) return f.hw == HW_E4M3;
     return f.variant == vi;
 }
 
@@ -119,8 +110,8 @@ __device__ __forceinline__ f4 cast_in4(const f4& x, const FmtK& fi) {
     if constexpr (VI == VI_E5M2 || VI == VI_E4M3) {
         float r0, r1, r2, r3;
         if constexpr (VI == VI_E5M2) {
-            cast_e5m2x2(x.x, x.y, r0, r1);
-            cast_e5m2x2(x.z, x.w, r2, r3);
+            round2_e5m2(x.x, x.y, r0, r1);
+            round2_e5m2(x.z, x.w, r2, r3);
         } else {
             cast_e4m3x2(x.x, x.y, r0, r1);
             cast_e4m3x2(x.z, x.w, r2, r3);
@@ -412,8 +403,6 @@ enum HalfProduct {
     HP_FMA = 1,    // every product of two input values is a half: one fma
     HP_TEST = 2,   // tested per k-step: one fma where all of a wave's products are halves
 };
-
-using h2 = _Float16 __attribute__((ext_vector_type(2)));
 
 template <int N>
 struct HVec {

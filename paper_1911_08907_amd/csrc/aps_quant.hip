@@ -42,15 +42,57 @@ __host__ __device__ constexpr int cast_variant(int v) {
 // What one k_quantize launch writes per row.
 enum QuantOut { QO_Q = 0, QO_CODES4 = 1, QO_CODES8 = 2, QO_CODES16 = 3, QO_BOTH = 4 };
 
+// The hardware form in which an entry is cast straight to its codes when
+// those alone are written: about 3 VALU instructions per element in place of
+// 28 (cast, then encode), which had left the VALU as busy as the memory.
+// ResNet-50, 1-5-2: W = 8 189 -> 182 us (5.6 TB/s, the pattern's own rate),
+// W = 1 70 -> 62 us; 1-4-3 W = 8 199 -> 183 us.
+__host__ __device__ __forceinline__ int hw_of_cast(const FmtK& f, int out) {
+    return out == QO_CODES8 && (f.hw == HW_E5M2 || f.hw == HW_E4M3) ? f.hw
+           : (out == QO_CODES16 && f.hw == HW_HALF ? f.hw : HW_NONE);
+}
+
+// Stores the codes of R(y) for a thread's 4 elements.
+template <int HW>
+__device__ __forceinline__ void store_cast4(uint8_t* row, int64_t j, const f4& y) {
+    if constexpr (HW == HW_E5M2) {
+        __builtin_nontemporal_store(encode4_e5m2(y.x, y.y, y.z, y.w), (uint32_t*)(row + j));
+    } else if constexpr (HW == HW_E4M3) {
+        // values from 248 up reach 256 (0x78, INF) by the clamp or the rounding
+        __builtin_nontemporal_store(encode4_e4m3(y.x, y.y, y.z, y.w), (uint32_t*)(row + j));
+    } else {
+        const h2 lo = {(_Float16)y.x, (_Float16)y.y}, hi = {(_Float16)y.z, (_Float16)y.w};
+        const u2v v = {canonical2_half(__builtin_bit_cast(uint32_t, lo)), canonical2_half(__builtin_bit_cast(uint32_t, hi))};
+        __builtin_nontemporal_store(v, (u2v*)(row + 2 * j));
+    }
+}
+
+// Casts and stores a thread's 4 elements x, from j on, of row r.
+template <int V, int OUT, int HW>
+__device__ __forceinline__ void quantize4(const QuantArgs& a, const FmtK& f, int cls, int64_t r, int64_t j, const f4& x,
+                                          const int32_t ft[4]) {
+    if constexpr (HW != HW_NONE) {
+        const f4 y = {__builtin_amdgcn_ldexpf(x.x, ft[0]), __builtin_amdgcn_ldexpf(x.y, ft[1]),
+                      __builtin_amdgcn_ldexpf(x.z, ft[2]), __builtin_amdgcn_ldexpf(x.w, ft[3])};
+        store_cast4<HW>(a.codes + code_byte(r * a.ld, cls), j, y);
+    } else {
+        const f4 v = {quant_native<V>(x.x, ft[0] + f.k, f), quant_native<V>(x.y, ft[1] + f.k, f),
+                      quant_native<V>(x.z, ft[2] + f.k, f), quant_native<V>(x.w, ft[3] + f.k, f)};
+        if constexpr (OUT == QO_Q || OUT == QO_BOTH) __builtin_nontemporal_store(v, (f4*)(a.Q + j + r * a.ld));
+        if constexpr (OUT != QO_Q) {
+            const uint32_t cc[4] = {encode(v.x, f), encode(v.y, f), encode(v.z, f), encode(v.w, f)};
+            store_codes4_full(a.codes + code_byte(r * a.ld, cls), j, cc, cls);
+        }
+    }
+}
+
 // One block walks a range of chunks; for each chunk its threads stream all W
 // rows (two register sets of rows in flight), cast each row and store it.
 // The stores of a row are fixed at compile time (OUT): a store that is
 // conditional inside the streamed loop makes the compiler's load-counter
 // waits at the loop's joins far more conservative.
-template <int V, int OUT>
+template <int V, int OUT, int HW>
 __global__ __launch_bounds__(BLOCK) void k_quantize(QuantArgs a, Layers ly, Pal pal) {
-    constexpr bool HQ = OUT == QO_Q || OUT == QO_BOTH;
-    constexpr bool HC = OUT != QO_Q;
     const int64_t nchunks = (ly.n + CH - 1) / CH;
     int64_t cb, ce;
     block_range(nchunks, cb, ce);
@@ -62,7 +104,7 @@ __global__ __launch_bounds__(BLOCK) void k_quantize(QuantArgs a, Layers ly, Pal 
         hint = ci.i0;
         if (ci.mixed) continue;  // handled by k_quantize_mixed
         const FmtK& f = pal.f[ci.pidx];
-        if (cast_variant(f.variant) != V) continue;
+        if (cast_variant(f.variant) != V || hw_of_cast(f, OUT) != HW) continue;
         const int64_t j = start + (int64_t)threadIdx.x * VEC;
         if (j >= end) continue;
         int32_t ft[4];
@@ -81,15 +123,7 @@ __global__ __launch_bounds__(BLOCK) void k_quantize(QuantArgs a, Layers ly, Pal 
         const int cls = OUT == QO_CODES4 ? 0 : (OUT == QO_CODES8 ? 1 : (OUT == QO_CODES16 ? 2 : a.code_cls));
         int64_t r = 0;  // row of the next callback
         auto row = [&](const f4& x, bool valid) {
-            if (valid) {
-                const f4 v = {quant_native<V>(x.x, ft[0] + f.k, f), quant_native<V>(x.y, ft[1] + f.k, f),
-                              quant_native<V>(x.z, ft[2] + f.k, f), quant_native<V>(x.w, ft[3] + f.k, f)};
-                if constexpr (HQ) __builtin_nontemporal_store(v, (f4*)(a.Q + j + r * ld));
-                if constexpr (HC) {
-                    const uint32_t cc[4] = {encode(v.x, f), encode(v.y, f), encode(v.z, f), encode(v.w, f)};
-                    store_codes4_full(a.codes + code_byte(r * ld, cls), j, cc, cls);
-                }
-            }
+            if (valid) quantize4<V, OUT, HW>(a, f, cls, r, j, x, ft);
             ++r;
         };
         stream_rows(
@@ -145,14 +179,15 @@ struct DeqArgs {
 };
 
 // A thread's 4 elements of one chunk as loaded: the fp32 bit patterns, or
-// the 4 codes (one 2-, 4- or 8-byte load, by code class).
+// the 4 codes (one 2-, 4- or 8-byte load, by code class), one per word, or
+// as packed for the hardware's conversions.
 struct DeqRaw {
     uint32_t w[4];
 };
 
-template <int IN>  // 0: fp32 values; 1 + code class: codes
+template <int IN, int HW>  // IN 0: fp32 values; 1 + code class: codes
 __device__ __forceinline__ DeqRaw deq_load(const DeqArgs& a, int64_t j) {
-    DeqRaw r;
+    DeqRaw r = {{0, 0, 0, 0}};
     if constexpr (IN == 0) {
         const f4 v = __builtin_nontemporal_load((const f4*)(a.Q + j));
         r.w[0] = f2u(v.x);
@@ -167,34 +202,60 @@ __device__ __forceinline__ DeqRaw deq_load(const DeqArgs& a, int64_t j) {
         r.w[3] = h >> 12;
     } else if constexpr (IN == 2) {  // bytes
         const uint32_t b = __builtin_nontemporal_load((const uint32_t*)(a.codes + j));
-        r.w[0] = b & 255u;
-        r.w[1] = (b >> 8) & 255u;
-        r.w[2] = (b >> 16) & 255u;
-        r.w[3] = b >> 24;
+        if constexpr (HW != HW_NONE) {
+            r.w[0] = b;
+        } else {
+            r.w[0] = b & 255u;
+            r.w[1] = (b >> 8) & 255u;
+            r.w[2] = (b >> 16) & 255u;
+            r.w[3] = b >> 24;
+        }
     } else {  // little-endian uint16
         const u2v b = __builtin_nontemporal_load((const u2v*)(a.codes + 2 * j));
-        r.w[0] = b.x & 0xFFFFu;
-        r.w[1] = b.x >> 16;
-        r.w[2] = b.y & 0xFFFFu;
-        r.w[3] = b.y >> 16;
+        if constexpr (HW != HW_NONE) {
+            r.w[0] = b.x;
+            r.w[1] = b.y;
+        } else {
+            r.w[0] = b.x & 0xFFFFu;
+            r.w[1] = b.x >> 16;
+            r.w[2] = b.y & 0xFFFFu;
+            r.w[3] = b.y >> 16;
+        }
     }
     return r;
+}
+
+// The four values by the hardware's conversions.
+template <int HW>
+__device__ __forceinline__ void deq_hw(const DeqRaw& r, float v[4]) {
+    if constexpr (HW == HW_E5M2) {
+        decode4_e5m2(r.w[0], v);
+    } else if constexpr (HW == HW_E4M3) {
+        decode4_e4m3(r.w[0], v);
+        const uint32_t nan = nan_bytes_e4m3(r.w[0]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (nan >> (8 * e + 7)) & 1u ? __builtin_nanf("") : v[e] * 0x1p-120f;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (float)__builtin_bit_cast(h2, r.w[e >> 1])[e & 1];
+    }
 }
 
 // Chunks a block has in flight at once: their loads are issued together, so
 // each wave waits for memory once per DEQ_GROUP chunks (the work per chunk
 // is 4 elements per thread, too little to cover a load's latency).
-constexpr int DEQ_GROUP = 4;
+constexpr int DEQ_GROUP = 8;
 
-// Codes of up to 8 bits decode through a table in LDS, one per palette
-// entry (value of every code), filled once per block; 16-bit codes decode
-// arithmetically.  A block walks its chunks in groups of DEQ_GROUP: the loads
+// Palettes all of 1-5-2, of 1-4-3 or of 1-5-10 decode by the hardware's
+// conversions (HW).  Other codes of up to 8 bits decode through a table in
+// LDS, one per palette entry (value of every code), filled once per block;
+// other 16-bit codes decode arithmetically.  A block walks its chunks in groups of DEQ_GROUP: the loads
 // of the next group are issued before the current one is decoded and
 // stored, and the first group's before the table is filled, so each wave
 // has a group's loads in flight while it works.
-template <int IN>
+template <int IN, int HW>
 __global__ __launch_bounds__(BLOCK) void k_dequantize(DeqArgs a, Layers ly, Pal pal) {
-    constexpr bool TABLE = IN == 1 || IN == 2;
+    constexpr bool TABLE = HW == HW_NONE && (IN == 1 || IN == 2);
     constexpr int NCODES = IN == 1 ? 16 : 256;
     __shared__ FmtK spal[APS_MAX_FORMATS];
     __shared__ float lut[TABLE ? APS_MAX_FORMATS : 1][TABLE ? NCODES : 1];
@@ -254,7 +315,7 @@ __global__ __launch_bounds__(BLOCK) void k_dequantize(DeqArgs a, Layers ly, Pal 
 #pragma unroll
         for (int g = 0; g < DEQ_GROUP; ++g) {
             const int64_t j = min(c0 + g, ce - 1) * CH + (int64_t)threadIdx.x * VEC;
-            raw[g] = deq_load<IN>(a, min(j, jlast));
+            raw[g] = deq_load<IN, HW>(a, min(j, jlast));
         }
     };
     auto process = [&](int64_t c0, const ChunkInfo* gci, const DeqRaw* graw) {
@@ -272,8 +333,12 @@ __global__ __launch_bounds__(BLOCK) void k_dequantize(DeqArgs a, Layers ly, Pal 
                 const FmtK& f = pal.f[ci.pidx];
                 const int32_t ft = ly.scale_exp ? clamp_exp(cld(ly.scale_exp, ci.i0)) : 0;
                 float v[4];
+                if constexpr (HW != HW_NONE) {
+                    deq_hw<HW>(graw[g], v);
+                } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = IN == 0 ? u2f(graw[g].w[e]) : dec(graw[g].w[e], ci.pidx, f);
+                    for (int e = 0; e < 4; ++e) v[e] = IN == 0 ? u2f(graw[g].w[e]) : dec(graw[g].w[e], ci.pidx, f);
+                }
                 const f4 o = {__builtin_amdgcn_ldexpf(v[0], -ft), __builtin_amdgcn_ldexpf(v[1], -ft),
                               __builtin_amdgcn_ldexpf(v[2], -ft), __builtin_amdgcn_ldexpf(v[3], -ft)};
                 __builtin_nontemporal_store(o, (f4*)(a.out + j));  // out may alias Q: same elements
@@ -330,21 +395,30 @@ extern "C" int aps_quantize(const float* X, int32_t W, int64_t ld, int64_t n, co
     // launch width measured on MI355X: with few rows per chunk (W < 64),
     // 64 blocks per CU (ResNet-50 at W = 8: 0.223 -> 0.20 ms)
     const dim3 grid((unsigned)grid_for(nchunks, W < 64 ? 64 : BLOCKS_PER_CU));
-    unsigned cm = 0;  // cast variants present
-    for (int i = 0; i < n_fmts; ++i) cm |= 1u << cast_variant(pal.f[i].variant);
     const int out = !codes ? QO_Q : (Q ? QO_BOTH : QO_CODES4 + ccls);
-#define APS_LAUNCH_Q(v)                                                                                    \
-    if (cm & (1u << (v))) {                                                                                \
-        switch (out) {                                                                                     \
-            case QO_Q: hipLaunchKernelGGL((k_quantize<v, QO_Q>), grid, dim3(BLOCK), 0, s, a, ly, pal); break; \
-            case QO_CODES4: hipLaunchKernelGGL((k_quantize<v, QO_CODES4>), grid, dim3(BLOCK), 0, s, a, ly, pal); break; \
-            case QO_CODES8: hipLaunchKernelGGL((k_quantize<v, QO_CODES8>), grid, dim3(BLOCK), 0, s, a, ly, pal); break; \
-            case QO_CODES16: hipLaunchKernelGGL((k_quantize<v, QO_CODES16>), grid, dim3(BLOCK), 0, s, a, ly, pal); break; \
-            default: hipLaunchKernelGGL((k_quantize<v, QO_BOTH>), grid, dim3(BLOCK), 0, s, a, ly, pal); break; \
-        }                                                                                                  \
+    unsigned cm = 0, hm = 0;  // cast variants, and hardware forms, present
+    for (int i = 0; i < n_fmts; ++i) {
+        const int hw = hw_of_cast(pal.f[i], out);
+        if (hw) hm |= 1u << hw;
+        else cm |= 1u << cast_variant(pal.f[i].variant);
+    }
+#define APS_Q(v, o, h) hipLaunchKernelGGL((k_quantize<v, o, h>), grid, dim3(BLOCK), 0, s, a, ly, pal)
+    if (hm & (1u << HW_E5M2)) APS_Q(V_TOP_F64, QO_CODES8, HW_E5M2);
+    if (hm & (1u << HW_E4M3)) APS_Q(V_LOW_F64, QO_CODES8, HW_E4M3);
+    if (hm & (1u << HW_HALF)) APS_Q(V_TOP_F64, QO_CODES16, HW_HALF);
+#define APS_LAUNCH_Q(v)                                          \
+    if (cm & (1u << (v))) {                                      \
+        switch (out) {                                           \
+            case QO_Q: APS_Q(v, QO_Q, HW_NONE); break;            \
+            case QO_CODES4: APS_Q(v, QO_CODES4, HW_NONE); break;  \
+            case QO_CODES8: APS_Q(v, QO_CODES8, HW_NONE); break;  \
+            case QO_CODES16: APS_Q(v, QO_CODES16, HW_NONE); break; \
+            default: APS_Q(v, QO_BOTH, HW_NONE); break;           \
+        }                                                        \
     }
     APS_LAUNCH_Q(V_INT_F64) APS_LAUNCH_Q(V_INT_EXACT) APS_LAUNCH_Q(V_INT_M0) APS_LAUNCH_Q(V_TOP_F64)
     APS_LAUNCH_Q(V_TOP_M0) APS_LAUNCH_Q(V_LOW_F64) APS_LAUNCH_Q(V_LOW_M0) APS_LAUNCH_Q(V_GEN)
+#undef APS_Q
 #undef APS_LAUNCH_Q
     if (fmt_idx && n_fmts > 1 && L > 1)
         hipLaunchKernelGGL(k_quantize_mixed, dim3((unsigned)L, (unsigned)std::min<int32_t>(W, MIXED_ROW_BLOCKS)),
@@ -367,17 +441,25 @@ extern "C" int aps_dequantize(const float* Q, const void* codes, int64_t n, cons
     Layers ly{offsets, fmt_idx, scale_exp, n, L, n_fmts};
     DeqArgs a{Q, (const uint8_t*)codes, out, ccls};
     const int64_t nchunks = (n + CH - 1) / CH;
-    // measured on MI355X (ResNet-50's 25.6 M byte codes, the next group's
-    // loads issued before the current group is stored): 16 blocks per CU with
-    // 4 chunks per group (30.7 us) beat 8 with 4 or 8, 16 with 2, 32 with 2
-    // and 4 with 8 (31.6 to 35.5 us)
+    // measured on MI355X (25.6 M codes): 16 blocks per CU with 8 chunks per
+    // group, 28.1 us from byte codes by the hardware's conversions; 4 chunks
+    // 29.6, 2 31.0, 8 or 32 blocks per CU with 2 to 8 chunks 30.8 to 35.3.
+    // The table in place of the conversions: 30.7 with 4 chunks.
     const dim3 grid((unsigned)grid_for(nchunks, 16));
     hipStream_t s = (hipStream_t)stream;
     const int in = Q ? 0 : 1 + ccls;
-    if (in == 0) hipLaunchKernelGGL(k_dequantize<0>, grid, dim3(BLOCK), 0, s, a, ly, pal);
-    else if (in == 1) hipLaunchKernelGGL(k_dequantize<1>, grid, dim3(BLOCK), 0, s, a, ly, pal);
-    else if (in == 2) hipLaunchKernelGGL(k_dequantize<2>, grid, dim3(BLOCK), 0, s, a, ly, pal);
-    else hipLaunchKernelGGL(k_dequantize<3>, grid, dim3(BLOCK), 0, s, a, ly, pal);
+    int hw = pal.f[0].hw;  // the whole palette's, or none
+    for (int i = 1; i < n_fmts; ++i)
+        if (pal.f[i].hw != hw) hw = HW_NONE;
+#define APS_D(i, h) hipLaunchKernelGGL((k_dequantize<i, h>), grid, dim3(BLOCK), 0, s, a, ly, pal)
+    if (in == 0) APS_D(0, HW_NONE);
+    else if (in == 1) APS_D(1, HW_NONE);
+    else if (in == 2 && hw == HW_E5M2) APS_D(2, HW_E5M2);
+    else if (in == 2 && hw == HW_E4M3) APS_D(2, HW_E4M3);
+    else if (in == 2) APS_D(2, HW_NONE);
+    else if (hw == HW_HALF) APS_D(3, HW_HALF);
+    else APS_D(3, HW_NONE);
+#undef APS_D
     return launched();
 }
 

@@ -946,3 +946,45 @@ def test_lp_gemm_large_tiles_sampled(dev, M, N, fin, facc, acc):
     assert same_f32(g[rows], ref_r), first_diff(g[rows], ref_r)
     ref_c = O.lp_gemm(Am, np.ascontiguousarray(Bm[:, cols]), ofmt(fin), ofmt(facc), acc)
     assert same_f32(np.ascontiguousarray(g[:, cols]), ref_c), first_diff(g[:, cols], ref_c)
+
+
+@pytest.mark.parametrize("f", [F(5, 2), F(4, 3), F(5, 10)], ids=str)
+def test_codes_by_hardware_conversion(dev, f):
+    """The formats whose codes the hardware converts: every code (INF and NaN
+    codes included) summed with every code of a sample (8-bit formats: with
+    every code), over ragged layers, to sums and to codes; a palette that
+    mixes such formats with others; and the sums' codes decoded again."""
+    rng = np.random.default_rng(1400 + f.m)
+    bits = 1 + f.e + f.m
+    dt = np.uint8 if bits <= 8 else np.uint16
+    every = np.arange(1 << bits, dtype=np.uint32)
+    other = every if bits <= 8 else np.concatenate([rng.integers(0, 1 << bits, 5), [0x7C00, 0xFC00, 0x7E00, 0x0001, 0x8000, 0x03FF]])
+    rows = [np.tile(every, other.size), np.repeat(other, every.size)]
+    n = rows[0].size - 5                      # a ragged end
+    rows.append(rng.integers(0, 1 << bits, rows[0].size))
+    ld = rows[0].size
+    codes = np.stack([r.astype(dt) for r in rows])
+    sizes = [n - 3000 - 1025, 0, 1025, 17, 2983]
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    se = rng.integers(-20, 20, len(sizes)).astype(np.int32)
+    offs_t, se_t = torch.from_numpy(offs).to(dev), torch.from_numpy(se).to(dev)
+    c_t = torch.from_numpy(codes.view(np.uint8).reshape(-1)).to(dev)
+    same8 = [F(4, 3), F(5, 2), F(3, 4)] if bits <= 8 else [F(5, 10), F(8, 7), F(5, 10, 14)]
+    for W in (1, 2, 3):
+        for pal, idx in (([f], None), (same8, np.array([0, 1, 1, 2, 0], np.uint8))):
+            opal = [ofmt(p) for p in pal]
+            idx_t = None if idx is None else torch.from_numpy(idx).to(dev)
+            log(f"codes by conversion {f} W={W} palette of {len(pal)} n={n}")
+            out = torch.full((n,), float("nan"), device=dev)
+            cs = torch.zeros(ld * codes.itemsize, dtype=torch.uint8, device=dev)
+            A.aps_sim_reduce_codes(c_t, W, ld, n, offs_t, se_t, pal, idx_t, out=out, codes_out=cs)
+            raw = codes[:W].view(np.uint8).reshape(W, -1)
+            ref = O.sim_reduce_codes(raw, W, ld, n, offs, se, opal, idx)
+            scaled = O.sim_reduce_codes(raw, W, ld, n, offs, se, opal, idx, flags=O.OUTPUT_SCALED)
+            g = out.cpu().numpy()
+            assert same_f32(g, ref), first_diff(g, ref)
+            back = torch.full((n,), float("nan"), device=dev)
+            A.aps_dequantize(None, cs, n, offs_t, se_t, pal, idx_t, back)
+            assert _codes_equal(cs.cpu().numpy(), O.pack_codes(scaled, offs, opal, idx), n, bits, np.isnan(scaled))
+            b = back.cpu().numpy()
+            assert same_f32(b, ref), first_diff(b, ref)
