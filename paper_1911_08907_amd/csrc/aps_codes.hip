@@ -78,12 +78,11 @@ __global__ __launch_bounds__(BLOCK) void k_sim_reduce_codes(CodesArgs a, Layers 
     const int64_t nchunks = (ly.n + CHC - 1) / CHC;
     int64_t cb, ce;
     block_range(nchunks, cb, ce);
-    int hint = 0;
+    LayerCur cur{-1, 0};
     for (int64_t c = cb; c < ce; ++c) {
         const int64_t start = c * CHC;
         const int64_t end = min(start + CHC, ly.n);
-        const ChunkInfo ci = chunk_layers(ly, start, end, hint);
-        hint = ci.i0;
+        const ChunkInfo ci = chunk_layers(ly, start, end, cur);
         if (ci.mixed) continue;
         const FmtK& f = pal.f[ci.pidx];
         if (f.variant != V || hw_of_codes(f, CC) != HW) continue;
@@ -303,7 +302,7 @@ __global__ __launch_bounds__(BLOCK) void k_sim_reduce_codes_mixed(CodesArgs a, L
     const int64_t start = pb / CHC * CHC;
     const int64_t end = min(start + CHC, ly.n);
     if (cld(ly.offsets, b - 1) > start) return;
-    if (!chunk_layers(ly, start, end, 0).mixed) return;
+    if (!chunk_layers(ly, start, end).mixed) return;
     for (int64_t j0 = start + 2 * (int64_t)threadIdx.x; j0 < end; j0 += 2 * BLOCK) {
         uint32_t cd[2] = {0, 0};
         for (int e = 0; e < 2; ++e) {

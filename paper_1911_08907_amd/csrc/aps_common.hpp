@@ -407,19 +407,65 @@ __device__ __forceinline__ int find_layer(const int64_t* __restrict__ off, int L
     return lo;
 }
 
+// A position in the layers, uniform: a layer and where it ends.
+struct LayerCur {
+    int i;         // layer of the last position looked up; -1 before the first
+    int64_t next;  // offsets[i + 1]
+};
+
+// Moves the cursor to the largest i with offsets[i] <= pos (pos < n).  The 64
+// lanes read 64 evenly spaced offsets at once and narrow the range to one
+// step of them, so a search takes one read up to 64 layers, two up to 4096,
+// where a binary search is a chain of 6 to 12 dependent scalar loads (it had
+// been a third of a small launch's time).  Every lane of the wave calls it.
+__device__ __forceinline__ void layer_seek(const Layers& ly, int64_t pos, LayerCur& cu) {
+    const int lane = threadIdx.x & 63;
+    int lo = 0, hi = ly.L;
+    int64_t hv = ly.n;  // offsets[hi]
+    do {
+        const int step = (hi - lo + 63) >> 6;
+        const int idx = lo + lane * step;
+        const int64_t v = idx < hi ? ly.offsets[idx] : INT64_MAX;
+        const int cnt = __builtin_popcountll(__ballot(v <= pos));  // >= 1: offsets[lo] <= pos
+        const int nlo = lo + (cnt - 1) * step;
+        if (nlo + step < hi) {  // lane cnt holds the offset above
+            hv = (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)((uint64_t)v >> 32), cnt) << 32 |
+                           (uint32_t)__builtin_amdgcn_readlane((int)v, cnt));
+            hi = nlo + step;
+        }
+        lo = nlo;
+    } while (hi - lo > 1);
+    cu.i = lo;
+    cu.next = hv;
+}
+
 // Layers of chunk [start, end): first i0, last i1 (uniform); whether they all
-// use one palette entry, and which.
+// use one palette entry, and which.  The cursor moves to the last of them, so
+// walking the chunks in order reads the offsets only where a layer ends.
 struct ChunkInfo {
     int i0, i1, pidx;
     bool mixed;
 };
 
-__device__ __forceinline__ ChunkInfo chunk_layers(const Layers& ly, int64_t start, int64_t end, int hint) {
+__device__ __forceinline__ ChunkInfo chunk_layers(const Layers& ly, int64_t start, int64_t end, LayerCur& cu) {
     ChunkInfo ci;
-    ci.i0 = find_layer(ly.offsets, ly.L, start, hint);
-    int i = ci.i0;
-    while (cld(ly.offsets, i + 1) < end) ++i;  // offsets[L] = n >= end
-    ci.i1 = i;
+    if (cu.i < 0) {
+        layer_seek(ly, start, cu);
+    } else {
+        int s = 0;
+        while (cu.next <= start && s < 4) {
+            ++s;
+            ++cu.i;
+            cu.next = cld(ly.offsets, cu.i + 1);
+        }
+        if (cu.next <= start) layer_seek(ly, start, cu);
+    }
+    ci.i0 = cu.i;
+    while (cu.next < end) {  // offsets[L] = n >= end
+        ++cu.i;
+        cu.next = cld(ly.offsets, cu.i + 1);
+    }
+    ci.i1 = cu.i;
     ci.pidx = ly.fmt_idx ? cld_idx(ly.fmt_idx, ci.i0) : 0;
     ci.mixed = false;
     if (ly.fmt_idx && ci.i1 > ci.i0) {
@@ -429,6 +475,12 @@ __device__ __forceinline__ ChunkInfo chunk_layers(const Layers& ly, int64_t star
         }
     }
     return ci;
+}
+
+// The same for one chunk on its own.
+__device__ __forceinline__ ChunkInfo chunk_layers(const Layers& ly, int64_t start, int64_t end) {
+    LayerCur cu{-1, 0};
+    return chunk_layers(ly, start, end, cu);
 }
 
 // Per-element scale exponent for elements j..j+3 of a chunk spanning layers i0..i1.
@@ -828,7 +880,7 @@ __device__ __forceinline__ bool mixed_chunk_of_boundary(const Layers& ly, int b,
     start = c * CH;
     end = min(start + CH, ly.n);
     if (cld(ly.offsets, b - 1) > start) return false;  // an earlier boundary owns it
-    const ChunkInfo ci = chunk_layers(ly, start, end, 0);
+    const ChunkInfo ci = chunk_layers(ly, start, end);
     return ci.mixed;
 }
 

@@ -20,14 +20,13 @@ __global__ __launch_bounds__(BLOCK) void k_maxabs(const float* __restrict__ G, i
     const int64_t nchunks = (ly.n + CH - 1) / CH;
     int64_t cb, ce;
     block_range(nchunks, cb, ce);
-    int hint = 0;
+    LayerCur cur{-1, 0};
     uint32_t run = 0;      // running max for layer run_layer (uniform layer runs only)
     int run_layer = -1;
     for (int64_t c = cb; c < ce; ++c) {
         const int64_t start = c * CH;
         const int64_t end = min(start + CH, ly.n);
-        const ChunkInfo ci = chunk_layers(ly, start, end, hint);
-        hint = ci.i0;
+        const ChunkInfo ci = chunk_layers(ly, start, end, cur);
         const int64_t j = start + (int64_t)threadIdx.x * VEC;
         uint32_t m0 = 0, m1 = 0, m2 = 0, m3 = 0;
         if (j < end) {
@@ -102,14 +101,13 @@ __global__ __launch_bounds__(BLOCK) void k_sim_reduce(ReduceArgs a, Layers ly, P
     const int64_t nchunks = (ly.n + CH - 1) / CH;
     int64_t cb, ce;
     block_range(nchunks, cb, ce);
-    int hint = 0;
+    LayerCur cur{-1, 0};
     PendingOut pd;
     pd.valid = false;
     for (int64_t c = cb; c < ce; ++c) {
         const int64_t start = c * CH;
         const int64_t end = min(start + CH, ly.n);
-        const ChunkInfo ci = chunk_layers(ly, start, end, hint);
-        hint = ci.i0;
+        const ChunkInfo ci = chunk_layers(ly, start, end, cur);
         if (ci.mixed) continue;  // handled by k_sim_reduce_mixed
         const FmtK& f = pal.f[ci.pidx];
         if (f.variant != V) continue;  // another launch owns this format

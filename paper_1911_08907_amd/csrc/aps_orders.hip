@@ -102,14 +102,13 @@ __global__ __launch_bounds__(BLOCK) void k_sim_reduce_ex(ReduceArgs a, Layers ly
     const int64_t nchunks = (ly.n + CH - 1) / CH;
     int64_t cb, ce;
     block_range(nchunks, cb, ce);
-    int hint = 0;
+    LayerCur cur{-1, 0};
     PendingOut pd;
     pd.valid = false;
     for (int64_t c = cb; c < ce; ++c) {
         const int64_t start = c * CH;
         const int64_t end = min(start + CH, ly.n);
-        const ChunkInfo ci = chunk_layers(ly, start, end, hint);
-        hint = ci.i0;
+        const ChunkInfo ci = chunk_layers(ly, start, end, cur);
         const int64_t seg = ring_segment(start, ly.n, od.ng);
         // chunks that mix palette entries: k_sim_reduce_ex_slow; chunks that
         // cross ring segments: k_sim_reduce_ex_cross
@@ -145,7 +144,7 @@ __global__ __launch_bounds__(BLOCK) void k_sim_reduce_ex_cross(ReduceArgs a, Lay
     const int64_t start = p / CH * CH;
     if (s1 > 1 && ((s1 - 1) * ly.n + od.ng - 1) / od.ng > start) return;  // an earlier boundary owns it
     const int64_t end = min(start + CH, ly.n);
-    const ChunkInfo ci = chunk_layers(ly, start, end, 0);
+    const ChunkInfo ci = chunk_layers(ly, start, end);
     if (ci.mixed) return;  // k_sim_reduce_ex_slow
     const FmtK& f = pal.f[ci.pidx];
     if (f.variant != V) return;
@@ -229,7 +228,7 @@ __global__ __launch_bounds__(BLOCK) void k_sim_reduce_ex_slow(ReduceArgs a, Laye
     const int64_t start = (int64_t)blockIdx.x * CH;
     if (start >= ly.n) return;
     const int64_t end = min(start + CH, ly.n);
-    const ChunkInfo ci = chunk_layers(ly, start, end, 0);
+    const ChunkInfo ci = chunk_layers(ly, start, end);
     if (!ci.mixed) return;
     for (int64_t j0 = start + 2 * (int64_t)threadIdx.x; j0 < end; j0 += 2 * BLOCK) {
         uint32_t cd[2] = {0, 0};

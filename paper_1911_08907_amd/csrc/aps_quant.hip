@@ -96,12 +96,11 @@ __global__ __launch_bounds__(BLOCK) void k_quantize(QuantArgs a, Layers ly, Pal 
     const int64_t nchunks = (ly.n + CH - 1) / CH;
     int64_t cb, ce;
     block_range(nchunks, cb, ce);
-    int hint = 0;
+    LayerCur cur{-1, 0};
     for (int64_t c = cb; c < ce; ++c) {
         const int64_t start = c * CH;
         const int64_t end = min(start + CH, ly.n);
-        const ChunkInfo ci = chunk_layers(ly, start, end, hint);
-        hint = ci.i0;
+        const ChunkInfo ci = chunk_layers(ly, start, end, cur);
         if (ci.mixed) continue;  // handled by k_quantize_mixed
         const FmtK& f = pal.f[ci.pidx];
         if (cast_variant(f.variant) != V || hw_of_cast(f, OUT) != HW) continue;
@@ -291,7 +290,7 @@ __global__ __launch_bounds__(BLOCK) void k_dequantize(DeqArgs a, Layers ly, Pal 
         return;
     }
     if (cb >= ce) return;  // uniform per block
-    int hint = 0;
+    LayerCur cur{-1, 0};
     ChunkInfo cis[DEQ_GROUP];
     DeqRaw raw[DEQ_GROUP];
     // the chunks' layers first (scalar loads, wave-uniform), then the group's
@@ -299,17 +298,21 @@ __global__ __launch_bounds__(BLOCK) void k_dequantize(DeqArgs a, Layers ly, Pal 
     auto issue = [&](int64_t c0) {
         // usually the whole group lies in one layer: one lookup for all of it
         const int64_t gend = min(min(c0 + DEQ_GROUP, ce) * CH, ly.n);
-        const ChunkInfo gi = chunk_layers(ly, c0 * CH, gend, hint);
-        hint = __builtin_amdgcn_readfirstlane(gi.i0);
+        const LayerCur at = cur;
+        const ChunkInfo gi = chunk_layers(ly, c0 * CH, gend, cur);
         if (gi.i0 == gi.i1) {
 #pragma unroll
             for (int g = 0; g < DEQ_GROUP; ++g) cis[g] = gi;
         } else {
+            cur = at;  // chunk by chunk
 #pragma unroll
             for (int g = 0; g < DEQ_GROUP; ++g) {
-                const int64_t c = min(c0 + g, ce - 1);
-                cis[g] = chunk_layers(ly, c * CH, min(c * CH + CH, ly.n), hint);
-                hint = __builtin_amdgcn_readfirstlane(cis[g].i0);
+                const int64_t c = c0 + g;
+                if (c >= ce) {
+                    cis[g] = cis[g - 1];  // not used
+                    continue;
+                }
+                cis[g] = chunk_layers(ly, c * CH, min(c * CH + CH, ly.n), cur);
             }
         }
 #pragma unroll

@@ -184,7 +184,7 @@ __global__ __launch_bounds__(BLOCK) void k_sync_spec(SyncArgs a, SyncWs ws, Laye
     const int64_t nchunks = (ly.n + CH - 1) / CH;
     int64_t cb, ce;
     block_range(nchunks, cb, ce);
-    int hint = 0;
+    LayerCur cur{-1, 0};
     uint32_t run = 0;  // running max of layer run_layer (chunks inside one layer)
     int run_layer = -1;
     PendingSync pd;
@@ -193,8 +193,7 @@ __global__ __launch_bounds__(BLOCK) void k_sync_spec(SyncArgs a, SyncWs ws, Laye
     for (int64_t c = cb; c < ce; ++c) {
         const int64_t start = c * CH;
         const int64_t end = min(start + CH, ly.n);
-        const ChunkInfo ci = chunk_layers(ly, start, end, hint);
-        hint = ci.i0;
+        const ChunkInfo ci = chunk_layers(ly, start, end, cur);
         if (ci.mixed) continue;  // k_sync_spec_mixed
         const int64_t j = start + (int64_t)threadIdx.x * VEC;
         uint32_t mx0 = 0, mx1 = 0, mx2 = 0, mx3 = 0;
@@ -350,6 +349,8 @@ __device__ __forceinline__ void sync_layer(uint32_t maxabs_bits, int32_t N, cons
     }
 }
 
+constexpr int BOOK_OFFS = 1023;
+
 // Pass 2's bookkeeping in one launch; thread t handles layer t and chunk t.
 //  * Layer t: its exponent into scale_exp and its threshold into thr (the
 //    one-pass route), or the exponent and a mark in thr, 1 where the guess
@@ -363,8 +364,24 @@ __device__ __forceinline__ void sync_layer(uint32_t maxabs_bits, int32_t N, cons
 __global__ void k_sync_bookkeep(const uint32_t* __restrict__ maxabs, Layers ly, int32_t N, Pal pal,
                                 int32_t* __restrict__ scale_exp, SyncWs ws, bool guess) {
     __shared__ FmtK spal[APS_MAX_FORMATS];
+    // up to BOOK_OFFS layers their offsets are searched in LDS: eight or so
+    // dependent reads per chunk, which from memory are most of a small launch
+    __shared__ int32_t soff[BOOK_OFFS + 1];
+    const bool in_lds = ly.L <= BOOK_OFFS;
+    if (in_lds)
+        for (int i = threadIdx.x; i <= ly.L; i += blockDim.x) soff[i] = (int32_t)ly.offsets[i];
     pal_to_lds(pal, spal);
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    auto offset = [&](int i) -> int64_t { return in_lds ? soff[i] : ly.offsets[i]; };
+    // the largest i with offsets[i] <= pos
+    auto layer_of = [&](int64_t pos) {
+        int lo = 0, hi = ly.L;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (offset(mid) <= pos) lo = mid; else hi = mid;
+        }
+        return lo;
+    };
     // what decides a layer's repair: its threshold, or whether its guess was wrong
     auto layer_th = [&](int i, int32_t& r) {
         const FmtK& f = spal[ly.fmt_idx ? ly.fmt_idx[i] : 0];
@@ -389,12 +406,12 @@ __global__ void k_sync_bookkeep(const uint32_t* __restrict__ maxabs, Layers ly, 
         for (int wv = 0; wv < 4; ++wv)
             if (start + 256 * wv < end) cm = min(cm, (w4 >> (8 * wv)) & 0xFFu);
     }
-    const int i0 = find_layer(ly.offsets, ly.L, start, 0), i1 = find_layer(ly.offsets, ly.L, end - 1, i0);
+    const int i0 = layer_of(start);
     int32_t th = 0;
     bool mixed = false;
     const int p0 = ly.fmt_idx ? ly.fmt_idx[i0] : 0;
-    for (int i = i0; i <= i1; ++i) {
-        if (ly.offsets[i] == ly.offsets[i + 1]) continue;  // empty layer
+    for (int i = i0; i < ly.L && offset(i) < end; ++i) {
+        if (offset(i) == offset(i + 1)) continue;  // empty layer
         int32_t r;
         th = max(th, layer_th(i, r));
         if (ly.fmt_idx && ly.fmt_idx[i] != p0) mixed = true;
@@ -492,7 +509,7 @@ __global__ __launch_bounds__(BLOCK) void k_sync_repair(ReduceArgs a, Layers ly, 
     for (int64_t k = wave; k < total; k += nw) {
         const int64_t start = (int64_t)cld(ws.list, every ? k >> 2 : k) * CH;
         const int64_t end = min(start + CH, ly.n);
-        const ChunkInfo ci = chunk_layers(ly, start, end, 0);
+        const ChunkInfo ci = chunk_layers(ly, start, end);
         const FmtK& f = pal.f[ci.pidx];
         if (f.variant != V) continue;  // another launch owns this format
         if (ws.half) {
@@ -644,7 +661,7 @@ __global__ __launch_bounds__(BLOCK) void k_guess_spec(ReduceArgs a, Layers ly, P
     const int64_t nchunks = (ly.n + CH - 1) / CH;
     int64_t cb, ce;
     block_range(nchunks, cb, ce);
-    int hint = 0;
+    LayerCur cur{-1, 0};
     uint32_t run = 0;  // running max of layer run_layer (chunks inside one layer)
     int run_layer = -1;
     PendingOut pd;
@@ -652,8 +669,7 @@ __global__ __launch_bounds__(BLOCK) void k_guess_spec(ReduceArgs a, Layers ly, P
     for (int64_t c = cb; c < ce; ++c) {
         const int64_t start = c * CH;
         const int64_t end = min(start + CH, ly.n);
-        const ChunkInfo ci = chunk_layers(ly, start, end, hint);
-        hint = ci.i0;
+        const ChunkInfo ci = chunk_layers(ly, start, end, cur);
         if (ci.mixed) continue;
         const FmtK& f = pal.f[ci.pidx];
         if (f.variant != V) continue;  // another launch owns this format

@@ -988,3 +988,23 @@ def test_codes_by_hardware_conversion(dev, f):
             assert _codes_equal(cs.cpu().numpy(), O.pack_codes(scaled, offs, opal, idx), n, bits, np.isnan(scaled))
             b = back.cpu().numpy()
             assert same_f32(b, ref), first_diff(b, ref)
+
+
+@pytest.mark.parametrize("L", [1, 63, 64, 65, 200, 4096, 4200])
+def test_layer_lookup_over_many_layers(dev, L):
+    """The layers' lookup by 64 offsets at a time: layer counts around one, two
+    and three rounds of it, runs of empty layers at the start, in the middle
+    and at the end, and chunks that start inside, at the start and at the end
+    of a layer; a quarter of the layers in another format."""
+    rng = np.random.default_rng(1500 + L)
+    sizes = rng.choice([0, 0, 1, 3, 40, 700], L)
+    sizes[: L // 8] = 0
+    sizes[L // 2: L // 2 + L // 8] = 0
+    sizes[L - L // 8:] = 0
+    sizes[L // 3] += 1024 - int(sizes[: L // 3 + 1].sum()) % 1024   # a layer ends at a chunk's end
+    sizes[L // 4] += 5000
+    offs, n, ld = _layout([int(v) for v in sizes])
+    G = _values(rng, 3, ld, offs, "normal")
+    run_case(dev, G, n, offs, [F(5, 2)], mode="aps", tag=f"L={L} n={n}")
+    idx = (rng.random(L) < 0.25).astype(np.uint8)
+    run_case(dev, G, n, offs, [F(5, 2), F(4, 3)], fmt_idx=idx, mode="aps", tag=f"L={L} n={n} two formats")
