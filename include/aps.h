@@ -242,6 +242,13 @@ int aps_sync_route(int32_t W, int64_t n, const aps_format* fmts, int32_t n_fmts,
  * The two-pass route: pass 1 is aps_layer_maxabs, pass 2 aps_layer_scales
  * followed by aps_sim_reduce.
  *
+ * Small sets.  With both passes in one call, no route bit and one format (no
+ * fmt_idx, or one palette entry), a set of at most 2^20 elements and 2^24
+ * element-workers, which stays in the caches, runs as two launches whatever
+ * route it would take: the maxima per 256 elements and layer, then the
+ * exponents and the scaled sums.  aps_sync_route names the route that larger
+ * sets, and separate passes, take with the same rule.
+ *
  * Route choice: APS_SYNC_TWO_PASS and APS_SYNC_GUESS force their routes;
  * APS_SYNC_ONE_PASS takes the one-pass route wherever it applies (else two
  * passes).  With no route bit, the one-pass route is taken where it applies

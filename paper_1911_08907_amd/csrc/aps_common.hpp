@@ -952,5 +952,11 @@ static inline unsigned variant_mask(const Pal& pal, int32_t n_fmts) {
 
 }  // namespace aps
 
+namespace aps {
+// aps_sync of a small set in two launches (aps_small.hip); part: ceil(n / 256) + L words.
+void launch_sync_small(const ReduceArgs& a, const Layers& ly, const FmtK& f, uint32_t* part, uint32_t* maxabs,
+                       int32_t* scale_exp, hipStream_t s);
+}  // namespace aps
+
 // The kernels are templates over the variant; dispatch table per entry point.
 #define APS_FOR_VARIANTS(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10)

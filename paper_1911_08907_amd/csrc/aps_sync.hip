@@ -761,6 +761,17 @@ extern "C" uint64_t aps_sync_workspace_bytes(int64_t n, int32_t L) {
 // cost more than they save on smaller ones), else two passes.
 constexpr int64_t GUESS_MIN_WORK = (int64_t)1 << 26;
 
+// Sets up to this size, of one format and with no route asked for, take the
+// two launches of aps_small.hip instead of the route's four or more.  Their
+// second launch reads all of a layer's unit maxima in every unit, which grows
+// with n squared, and all rows a second time, from the caches.  Measured on
+// MI355X, us per call in a graph, the route's launches against these: MLP
+// W = 2 15.0 and 7.9, ResNet-20 W = 8 21.2 and 10.1, 1 M elements W = 8 28.2
+// and 18.6, W = 13 31.2 and 26.0, 0.3 M W = 40 29.5 and 23.6; beyond, 2 M
+// W = 8 40.0 and 39.9, 5 M W = 3 49.3 and 114, 0.1 M W = 256 53 and 63.
+constexpr int64_t SMALL_MAX_N = (int64_t)1 << 20;
+constexpr int64_t SMALL_MAX_WORK = (int64_t)1 << 24;
+
 static bool one_pass_applies(int32_t W, const Pal& pal, int32_t n_fmts) {
     if (W & (W - 1)) return false;
     for (int i = 0; i < n_fmts; ++i)
@@ -821,6 +832,12 @@ extern "C" int aps_sync(const float* G, int32_t W, int64_t ld, int64_t n, const 
               (int32_t*)(wb + lay.list), nullptr, (int32_t*)(wb + lay.guess), wb + lay.listed, W >= SYNC_BYTES_MIN_W};
     Layers ly{offsets, fmt_idx, scale_exp, n, L, n_fmts};
     const int route = sync_route(W, n, pal, n_fmts, flags);
+    if (phases == (APS_SYNC_PASS1 | APS_SYNC_PASS2) && !(flags & ROUTE_BITS) && (n_fmts == 1 || !fmt_idx) &&
+        n <= SMALL_MAX_N && (int64_t)W * n <= SMALL_MAX_WORK) {
+        launch_sync_small(ReduceArgs{G, out, nullptr, ld, W, 0u, 0}, ly, pal.f[0], (uint32_t*)workspace, maxabs_bits,
+                          scale_exp, s);
+        return launched();
+    }
     if (route == APS_SYNC_ROUTE_ONE_PASS && W >= SYNC_HALF_MIN_W) {
         bool narrow = true;
         for (int i = 0; i < n_fmts; ++i) narrow = narrow && pal.f[i].m <= 7;

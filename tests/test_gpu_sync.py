@@ -637,3 +637,24 @@ def test_sync_hip_graph_replays(dev, route, W):
         g = out.cpu().numpy()
         assert same_f32(g, o_out), f"replay {trial} {first_diff(g, o_out)}"
         assert torch.equal(out.view(torch.int32), eager.view(torch.int32)), f"replay {trial} vs eager"
+
+
+@pytest.mark.parametrize("f", [F(5, 2), F(4, 3), F(3, 0), F(5, 10), F(5, 12), F(8, 23), F(2, 0), F(8, 7, 130)], ids=str)
+def test_sync_small_sets(dev, f):
+    """The default call on sets of a few units of 256 elements (two launches):
+    unit edges, layers inside a unit, over many units and empty ones at both
+    ends, worker counts around the register sets, every kind of value; and
+    the two sides of the size limit."""
+    rng = np.random.default_rng(zlib.crc32(f"small/{f}".encode()))
+    layouts = [[1], [255, 2], [0, 0, 256, 0, 256, 0], [100, 1, 155, 257, 3, 0, 1000], [7] * 80, [1] * 300 + [5000] + [2] * 9]
+    for sizes in layouts:
+        offs, n, ld = _layout(sizes)
+        for W in (1, 3, 8, 13, 70):
+            for kind in ("normal", "special", "tiny"):
+                G = _values(rng, W, ld, offs, kind)
+                sync_case(dev, G, n, offs, [f], tag=f"{f} small n={n} L={len(sizes)} W={W} {kind}", route=0)
+    if f.m == 2:
+        for n, W in (((1 << 20), 2), ((1 << 20) + 4, 2), (1 << 18, 64), ((1 << 18) + 4, 64)):
+            offs, n, ld = _layout([n - 3000, 2999, 1])
+            G = _values(rng, W, ld, offs, "normal")
+            sync_case(dev, G, n, offs, [f], tag=f"{f} limit n={n} W={W}", route=0)
