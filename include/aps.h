@@ -239,8 +239,9 @@ int aps_sync_route(int32_t W, int64_t n, const aps_format* fmts, int32_t n_fmts,
  * chunk of a layer whose guess differs.  The results never depend on the
  * guess; its cost is ceil(W/32) rows read plus the rerun layers.
  *
- * The two-pass route: pass 1 is aps_layer_maxabs, pass 2 aps_layer_scales
- * followed by aps_sim_reduce.
+ * The two-pass route: pass 1 is aps_layer_maxabs, pass 2 what
+ * aps_layer_scales followed by aps_sim_reduce computes (one launch when every
+ * layer has the same format).
  *
  * Small sets.  With both passes in one call, no route bit and one format (no
  * fmt_idx, or one palette entry), a set of at most 2^20 elements and 2^24

@@ -382,6 +382,42 @@ __device__ __forceinline__ uint32_t load_code(const uint8_t* row, int64_t j, int
     return *(const uint16_t*)(row + 2 * j);
 }
 
+// ========================================================= K2: scales
+
+__device__ __forceinline__ int ceil_log2_bits(uint32_t t) {
+    // t: bits of a finite positive fp32
+    const uint32_t ef = t >> 23, frac = t & 0x7FFFFFu;
+    if (ef == 0) {  // subnormal: t = frac * 2^-149
+        const int fl = 31 - __builtin_clz(frac);
+        return fl - 149 + ((frac & (frac - 1u)) ? 1 : 0);
+    }
+    return (int)ef - 127 + (frac ? 1 : 0);
+}
+
+// The scale exponent of a layer: emax - ceil(log2 fl32(N * ghat)), 0 where
+// that is no finite positive number.
+__device__ __forceinline__ int32_t scale_of(uint32_t maxabs_bits, int32_t N, int32_t emax) {
+    const uint32_t gb = maxabs_bits & 0x7FFFFFFFu;
+    if (gb == 0 || gb >= 0x7F800000u) return 0;
+    const uint32_t tb = f2u((float)N * u2f(gb));  // fl32(N * ghat), N <= 2^24 is exact in fp32
+    return tb < 0x7F800000u ? emax - ceil_log2_bits(tb) : 0;
+}
+
+// What a launch of the rounded sum reads and writes.
+struct ReduceArgs {
+    const float* __restrict__ G;
+    float* __restrict__ out;
+    uint8_t* __restrict__ codes;
+    int64_t ld;
+    int32_t W;
+    uint32_t flags;
+    int32_t code_cls;
+    // set: the exponents come from the layers' maxima (N = W) instead of
+    // ly.scale_exp, and are written to scale_out
+    const uint32_t* __restrict__ maxabs;
+    int32_t* __restrict__ scale_out;
+};
+
 // --------------------------------------------------------- chunk walking
 
 // Largest i in [0, L-1] with offsets[i] <= pos (pos < n), searching from a hint.
@@ -413,12 +449,33 @@ struct LayerCur {
     int64_t next;  // offsets[i + 1]
 };
 
-// Moves the cursor to the largest i with offsets[i] <= pos (pos < n).  The 64
-// lanes read 64 evenly spaced offsets at once and narrow the range to one
-// step of them, so a search takes one read up to 64 layers, two up to 4096,
-// where a binary search is a chain of 6 to 12 dependent scalar loads (it had
-// been a third of a small launch's time).  Every lane of the wave calls it.
+// Moves the cursor to the largest i with offsets[i] <= pos (pos < n): by a
+// binary search of scalar loads, which the scalar cache serves once a few
+// blocks of the CU have run.
 __device__ __forceinline__ void layer_seek(const Layers& ly, int64_t pos, LayerCur& cu) {
+    int lo = 0, hi = ly.L;
+    int64_t hv = ly.n;  // offsets[hi]
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        const int64_t v = cld(ly.offsets, mid);
+        if (v <= pos) {
+            lo = mid;
+        } else {
+            hi = mid;
+            hv = v;
+        }
+    }
+    cu.i = lo;
+    cu.next = hv;
+}
+
+// The same by 64 evenly spaced offsets at a time, one per lane, narrowing the
+// range to one step of them: one read up to 64 layers, two up to 4096.  Every
+// lane of the wave calls it.  Measured on MI355X, scalar against this one, us:
+// k_sync_spec's calls at W = 8, ResNet-50 176 and 170, BERT-large 2135 and
+// 2070, but W = 2 123 and 127; the guessed-scale route at W = 3 (BERT-large)
+// 2042 and 2159, the encode at W = 1 62 and 68: only k_sync_spec takes it.
+__device__ __forceinline__ void layer_seek_wave(const Layers& ly, int64_t pos, LayerCur& cu) {
     const int lane = threadIdx.x & 63;
     int lo = 0, hi = ly.L;
     int64_t hv = ly.n;  // offsets[hi]
@@ -447,10 +504,15 @@ struct ChunkInfo {
     bool mixed;
 };
 
+template <bool WAVE = false>  // the search by the whole wave
 __device__ __forceinline__ ChunkInfo chunk_layers(const Layers& ly, int64_t start, int64_t end, LayerCur& cu) {
     ChunkInfo ci;
+    const auto seek = [&]() {
+        if constexpr (WAVE) layer_seek_wave(ly, start, cu);
+        else layer_seek(ly, start, cu);
+    };
     if (cu.i < 0) {
-        layer_seek(ly, start, cu);
+        seek();
     } else {
         int s = 0;
         while (cu.next <= start && s < 4) {
@@ -458,7 +520,7 @@ __device__ __forceinline__ ChunkInfo chunk_layers(const Layers& ly, int64_t star
             ++cu.i;
             cu.next = cld(ly.offsets, cu.i + 1);
         }
-        if (cu.next <= start) layer_seek(ly, start, cu);
+        if (cu.next <= start) seek();
     }
     ci.i0 = cu.i;
     while (cu.next < end) {  // offsets[L] = n >= end
@@ -493,6 +555,29 @@ __device__ __forceinline__ void elem_scales(const Layers& ly, const ChunkInfo& c
     }
 }
 
+// The exponents of elements j..j+3 of a chunk: from the table, or from the
+// layers' maxima.
+__device__ __forceinline__ void chunk_scales(const ReduceArgs& a, const Layers& ly, const ChunkInfo& ci, int64_t j,
+                                             int32_t emax, int32_t ft[4]) {
+    if (!a.maxabs) {
+        if (ci.i0 != ci.i1) {
+            elem_scales(ly, ci, j, ft);
+            return;
+        }
+        ft[0] = ft[1] = ft[2] = ft[3] = ly.scale_exp ? clamp_exp(cld(ly.scale_exp, ci.i0)) : 0;
+        return;
+    }
+    if (ci.i0 == ci.i1) {
+        ft[0] = ft[1] = ft[2] = ft[3] = clamp_exp(scale_of(cld(a.maxabs, ci.i0), a.W, emax));
+        return;
+    }
+    int li = ci.i0;
+    for (int e = 0; e < 4; ++e) {
+        while (li < ci.i1 && ly.offsets[li + 1] <= j + e) ++li;
+        ft[e] = clamp_exp(scale_of(a.maxabs[li], a.W, emax));
+    }
+}
+
 __device__ __forceinline__ void block_range(int64_t nitems, int64_t& b, int64_t& e) {
     const int64_t G = gridDim.x;
     b = nitems * (int64_t)blockIdx.x / G;
@@ -519,18 +604,6 @@ __device__ __forceinline__ void block_max_atomic(uint32_t v, uint32_t* dst, uint
         if (t) atomicMax(dst, t);
     }
     __syncthreads();
-}
-
-// ========================================================= K2: scales
-
-__device__ __forceinline__ int ceil_log2_bits(uint32_t t) {
-    // t: bits of a finite positive fp32
-    const uint32_t ef = t >> 23, frac = t & 0x7FFFFFu;
-    if (ef == 0) {  // subnormal: t = frac * 2^-149
-        const int fl = 31 - __builtin_clz(frac);
-        return fl - 149 + ((frac & (frac - 1u)) ? 1 : 0);
-    }
-    return (int)ef - 127 + (frac ? 1 : 0);
 }
 
 // ========================================================= row streaming
@@ -615,15 +688,6 @@ __device__ __forceinline__ void stream_rows(int W, Load load, AfterIssue after_i
 
 // ===================================================== K4: sim reduce
 
-struct ReduceArgs {
-    const float* __restrict__ G;
-    float* __restrict__ out;
-    uint8_t* __restrict__ codes;
-    int64_t ld;
-    int32_t W;
-    uint32_t flags;
-    int32_t code_cls;
-};
 
 // A thread's finished outputs (4 elements), kept in registers until the next
 // chunk's first loads have been issued.  Loads and stores share one in-order
@@ -704,20 +768,18 @@ __device__ __forceinline__ void drain_if_full(const ReduceArgs& a, OutStage& st)
 // each of the 4 columns in mx (rows past the end read as -0: no effect).
 // With a stage (no codes), the previous chunk's outputs go to it instead of
 // straight to memory; the stage must have a free slot (drain_if_full).
-template <int V, bool MAX = false>
-__device__ __forceinline__ void reduce_vec(const ReduceArgs& a, const FmtK& f, int64_t j, int64_t lim,
-                                           const int32_t ft[4], PendingOut& pd, uint32_t* mx = nullptr,
+// scales(ft) gives the elements' exponents; it is called once the first rows'
+// loads are in flight, so that what it reads costs no trip of its own.  A
+// thread with j >= lim reads the 4 elements at j0 and keeps nothing.
+template <int V, bool MAX = false, class Scales>
+__device__ __forceinline__ void reduce_vec(const ReduceArgs& a, const FmtK& f, int64_t j, int64_t lim, int64_t j0,
+                                           Scales scales, PendingOut& pd, uint32_t* mx = nullptr,
                                            OutStage* st = nullptr) {
     const bool inq = a.flags & APS_INPUT_QUANTIZED;
     const bool outs = a.flags & APS_OUTPUT_SCALED;
     int F[4], Fo[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        F[e] = (inq ? 0 : ft[e]) + f.k;
-        Fo[e] = -((outs ? 0 : ft[e]) + f.k);
-    }
     bool bad0 = false, bad1 = false, bad2 = false, bad3 = false;
-    const float* p = a.G + j;
+    const float* p = a.G + j0;
     const int64_t ld = a.ld;
     float s0, s1, s2, s3;
     uint32_t m0 = 0, m1 = 0, m2 = 0, m3 = 0;
@@ -731,6 +793,13 @@ __device__ __forceinline__ void reduce_vec(const ReduceArgs& a, const FmtK& f, i
                 stage_out(pd, *st);
             else
                 flush_out(a, pd);
+            int32_t ft[4];
+            scales(ft);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                F[e] = (inq ? 0 : ft[e]) + f.k;
+                Fo[e] = -((outs ? 0 : ft[e]) + f.k);
+            }
         },
         [&](const f4& x) {
             if constexpr (MAX) {
@@ -779,7 +848,19 @@ __device__ __forceinline__ void reduce_vec(const ReduceArgs& a, const FmtK& f, i
     }
     pd.j = j;
     pd.lim = lim;
-    pd.valid = true;
+    pd.valid = j < lim;
+}
+
+template <int V, bool MAX = false>
+__device__ __forceinline__ void reduce_vec(const ReduceArgs& a, const FmtK& f, int64_t j, int64_t lim,
+                                           const int32_t ft[4], PendingOut& pd, uint32_t* mx = nullptr,
+                                           OutStage* st = nullptr) {
+    reduce_vec<V, MAX>(
+        a, f, j, lim, j,
+        [&](int32_t o[4]) {
+            for (int e = 0; e < 4; ++e) o[e] = ft[e];
+        },
+        pd, mx, st);
 }
 
 // ------------------------------------------------ chains of rounded adds
@@ -953,6 +1034,11 @@ static inline unsigned variant_mask(const Pal& pal, int32_t n_fmts) {
 }  // namespace aps
 
 namespace aps {
+// one palette entry for every layer
+static inline bool one_entry(const Layers& ly) { return ly.n_fmts == 1 || !ly.fmt_idx; }
+
+// The fused sum's launches (aps_core.hip); a.maxabs only with one palette entry.
+void launch_sim_reduce(const ReduceArgs& a, const Layers& ly, const Pal& pal, hipStream_t s);
 // aps_sync of a small set in two launches (aps_small.hip); part: ceil(n / 256) + L words.
 void launch_sync_small(const ReduceArgs& a, const Layers& ly, const FmtK& f, uint32_t* part, uint32_t* maxabs,
                        int32_t* scale_exp, hipStream_t s);

@@ -26,30 +26,34 @@ __global__ __launch_bounds__(BLOCK) void k_maxabs(const float* __restrict__ G, i
     for (int64_t c = cb; c < ce; ++c) {
         const int64_t start = c * CH;
         const int64_t end = min(start + CH, ly.n);
-        const ChunkInfo ci = chunk_layers(ly, start, end, cur);
         const int64_t j = start + (int64_t)threadIdx.x * VEC;
         uint32_t m0 = 0, m1 = 0, m2 = 0, m3 = 0;
-        if (j < end) {
-            const float* p = G + j;
-            // batches of MAXABS_UNROLL rows; rows past W-1 re-read row W-1,
-            // which leaves a maximum unchanged
-            for (int w = 0; w < W; w += MAXABS_UNROLL) {
-                f4 x[MAXABS_UNROLL];
+        const float* p = G + (j < end ? j : start);  // a thread past the end reads the chunk's start
+        // batches of MAXABS_UNROLL rows; rows past W-1 re-read row W-1,
+        // which leaves a maximum unchanged.  The chunk's layers are looked up
+        // with the first batch in flight.
+        ChunkInfo ci;
+        for (int w = 0; w < W; w += MAXABS_UNROLL) {
+            f4 x[MAXABS_UNROLL];
 #pragma unroll
-                for (int u = 0; u < MAXABS_UNROLL; ++u) x[u] = ld4(p + (int64_t)min(w + u, W - 1) * ld);
-#pragma unroll
-                for (int u = 0; u < MAXABS_UNROLL; ++u) {
-                    m0 = max(m0, f2u(x[u].x) & 0x7FFFFFFFu);
-                    m1 = max(m1, f2u(x[u].y) & 0x7FFFFFFFu);
-                    m2 = max(m2, f2u(x[u].z) & 0x7FFFFFFFu);
-                    m3 = max(m3, f2u(x[u].w) & 0x7FFFFFFFu);
-                }
+            for (int u = 0; u < MAXABS_UNROLL; ++u) x[u] = ld4(p + (int64_t)min(w + u, W - 1) * ld);
+            if (w == 0) {
+                __builtin_amdgcn_sched_barrier(0);
+                ci = chunk_layers(ly, start, end, cur);
             }
-            // elements past the end of the gradient (row padding) do not count
-            if (j + 1 >= end) m1 = 0;
-            if (j + 2 >= end) m2 = 0;
-            if (j + 3 >= end) m3 = 0;
+#pragma unroll
+            for (int u = 0; u < MAXABS_UNROLL; ++u) {
+                m0 = max(m0, f2u(x[u].x) & 0x7FFFFFFFu);
+                m1 = max(m1, f2u(x[u].y) & 0x7FFFFFFFu);
+                m2 = max(m2, f2u(x[u].z) & 0x7FFFFFFFu);
+                m3 = max(m3, f2u(x[u].w) & 0x7FFFFFFFu);
+            }
         }
+        // elements past the end of the gradient (row padding) do not count
+        if (j >= end) m0 = 0;
+        if (j + 1 >= end) m1 = 0;
+        if (j + 2 >= end) m2 = 0;
+        if (j + 3 >= end) m3 = 0;
         if (ci.i0 == ci.i1) {
             uint32_t v = max(max(m0, m1), max(m2, m3));
             if (ci.i0 != run_layer) {
@@ -81,19 +85,15 @@ __global__ void k_scales(const uint32_t* __restrict__ maxabs, int32_t L, int32_t
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= L) return;
     const FmtK& f = spal[fmt_idx ? fmt_idx[i] : 0];
-    const uint32_t gb = maxabs[i] & 0x7FFFFFFFu;
-    int32_t r = 0;
-    if (gb != 0 && gb < 0x7F800000u) {
-        const float t = (float)N * u2f(gb);  // fl32(N * ghat), N <= 2^24 is exact in fp32
-        const uint32_t tb = f2u(t);
-        if (tb < 0x7F800000u) r = f.emax - ceil_log2_bits(tb);
-    }
-    scale_exp[i] = r;
+    scale_exp[i] = scale_of(maxabs[i], N, f.emax);
 }
 
-// ST: the outputs go through an LDS stage (no codes written).
-template <int V, bool ST>
-__global__ __launch_bounds__(BLOCK) void k_sim_reduce(ReduceArgs a, Layers ly, Pal pal) {
+// ST: the outputs go through an LDS stage (no codes written).  ONE: the palette
+// has one entry, f1, so a chunk's rows can be asked for before its layers and
+// exponents are looked up (in a launch of a chunk or two per block that
+// lookup, a chain of three reads, had been a third of a block's time).
+template <int V, bool ST, bool ONE>
+__global__ __launch_bounds__(BLOCK) void k_sim_reduce(ReduceArgs a, Layers ly, Pal pal, FmtK f1) {
     __shared__ f4 st_o[ST ? OUT_STAGE * BLOCK : 1];
     __shared__ int32_t st_j[ST ? OUT_STAGE * BLOCK : 1];
     __shared__ int32_t st_lim[ST ? OUT_STAGE * BLOCK : 1];
@@ -104,9 +104,21 @@ __global__ __launch_bounds__(BLOCK) void k_sim_reduce(ReduceArgs a, Layers ly, P
     LayerCur cur{-1, 0};
     PendingOut pd;
     pd.valid = false;
+    if (ONE && a.maxabs)
+        for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < ly.L; i += (int64_t)gridDim.x * BLOCK)
+            a.scale_out[i] = scale_of(a.maxabs[i], a.W, f1.emax);
     for (int64_t c = cb; c < ce; ++c) {
         const int64_t start = c * CH;
         const int64_t end = min(start + CH, ly.n);
+        if constexpr (ONE) {
+            const int64_t j = start + (int64_t)threadIdx.x * VEC;
+            if constexpr (ST) drain_if_full(a, stage);
+            reduce_vec<V>(
+                a, f1, j, end, j < end ? j : start,
+                [&](int32_t ft[4]) { chunk_scales(a, ly, chunk_layers(ly, start, end, cur), j, f1.emax, ft); }, pd,
+                nullptr, ST ? &stage : nullptr);
+            continue;
+        }
         const ChunkInfo ci = chunk_layers(ly, start, end, cur);
         if (ci.mixed) continue;  // handled by k_sim_reduce_mixed
         const FmtK& f = pal.f[ci.pidx];
@@ -161,6 +173,25 @@ __global__ __launch_bounds__(BLOCK) void k_sim_reduce_mixed(ReduceArgs a, Layers
                                  : (uint8_t)((*pb & 0xF0u) | (c[0] & 15u));
         }
     }
+}
+
+void launch_sim_reduce(const ReduceArgs& a, const Layers& ly, const Pal& pal, hipStream_t s) {
+    const int64_t nchunks = (ly.n + CH - 1) / CH;
+    const dim3 grid((unsigned)stream_grid(nchunks, a.W, BLOCKS_PER_CU));
+    const bool one = one_entry(ly);
+    const unsigned vm = one ? 1u << pal.f[0].variant : variant_mask(pal, ly.n_fmts);
+#define APS_R(v, st, o) hipLaunchKernelGGL((k_sim_reduce<v, st, o>), grid, dim3(BLOCK), 0, s, a, ly, pal, pal.f[0])
+#define APS_LAUNCH_R(v)                             \
+    if (vm & (1u << (v))) {                         \
+        if (a.codes && one) APS_R(v, false, true);  \
+        else if (a.codes) APS_R(v, false, false);   \
+        else if (one) APS_R(v, true, true);         \
+        else APS_R(v, true, false);                 \
+    }
+    APS_FOR_VARIANTS(APS_LAUNCH_R)
+#undef APS_LAUNCH_R
+#undef APS_R
+    if (!one && ly.L > 1) hipLaunchKernelGGL(k_sim_reduce_mixed, dim3((unsigned)ly.L), dim3(BLOCK), 0, s, a, ly, pal);
 }
 
 }  // namespace aps
@@ -225,20 +256,6 @@ extern "C" int aps_sim_reduce(const float* G, int32_t W, int64_t ld, int64_t n, 
     if (n == 0) return APS_OK;
     hipStream_t s = (hipStream_t)stream;
     Layers ly{offsets, fmt_idx, scale_exp, n, L, n_fmts};
-    ReduceArgs a{G, out, (uint8_t*)codes_out, ld, W, flags, ccls};
-    const int64_t nchunks = (n + CH - 1) / CH;
-    const dim3 grid((unsigned)stream_grid(nchunks, W, BLOCKS_PER_CU));
-    const unsigned vm = variant_mask(pal, n_fmts);
-#define APS_LAUNCH_R(v)                                                                             \
-    if (vm & (1u << (v))) {                                                                         \
-        if (codes_out)                                                                              \
-            hipLaunchKernelGGL((k_sim_reduce<v, false>), grid, dim3(BLOCK), 0, s, a, ly, pal);       \
-        else                                                                                        \
-            hipLaunchKernelGGL((k_sim_reduce<v, true>), grid, dim3(BLOCK), 0, s, a, ly, pal);        \
-    }
-    APS_FOR_VARIANTS(APS_LAUNCH_R)
-#undef APS_LAUNCH_R
-    if (fmt_idx && n_fmts > 1 && L > 1)
-        hipLaunchKernelGGL(k_sim_reduce_mixed, dim3((unsigned)L), dim3(BLOCK), 0, s, a, ly, pal);
+    launch_sim_reduce(ReduceArgs{G, out, (uint8_t*)codes_out, ld, W, flags, ccls, nullptr, nullptr}, ly, pal, s);
     return launched();
 }

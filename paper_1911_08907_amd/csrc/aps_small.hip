@@ -97,14 +97,6 @@ __global__ __launch_bounds__(BLOCK) void k_small_max(const float* __restrict__ G
     }
 }
 
-// The scale exponent of a layer, as k_scales.
-__device__ __forceinline__ int32_t scale_of(uint32_t maxabs_bits, int32_t N, int32_t emax) {
-    const uint32_t gb = maxabs_bits & 0x7FFFFFFFu;
-    if (gb == 0 || gb >= 0x7F800000u) return 0;
-    const uint32_t tb = f2u((float)N * u2f(gb));
-    return tb < 0x7F800000u ? emax - ceil_log2_bits(tb) : 0;
-}
-
 // The maximum over a layer's units, by the whole wave.
 __device__ __forceinline__ uint32_t layer_max(const Layers& ly, const uint32_t* __restrict__ part, int i) {
     const int64_t u0 = cld(ly.offsets, i) / UNIT, u1 = (cld(ly.offsets, i + 1) - 1) / UNIT;

@@ -193,7 +193,7 @@ __global__ __launch_bounds__(BLOCK) void k_sync_spec(SyncArgs a, SyncWs ws, Laye
     for (int64_t c = cb; c < ce; ++c) {
         const int64_t start = c * CH;
         const int64_t end = min(start + CH, ly.n);
-        const ChunkInfo ci = chunk_layers(ly, start, end, cur);
+        const ChunkInfo ci = chunk_layers<true>(ly, start, end, cur);
         if (ci.mixed) continue;  // k_sync_spec_mixed
         const int64_t j = start + (int64_t)threadIdx.x * VEC;
         uint32_t mx0 = 0, mx1 = 0, mx2 = 0, mx3 = 0;
@@ -834,7 +834,7 @@ extern "C" int aps_sync(const float* G, int32_t W, int64_t ld, int64_t n, const 
     const int route = sync_route(W, n, pal, n_fmts, flags);
     if (phases == (APS_SYNC_PASS1 | APS_SYNC_PASS2) && !(flags & ROUTE_BITS) && (n_fmts == 1 || !fmt_idx) &&
         n <= SMALL_MAX_N && (int64_t)W * n <= SMALL_MAX_WORK) {
-        launch_sync_small(ReduceArgs{G, out, nullptr, ld, W, 0u, 0}, ly, pal.f[0], (uint32_t*)workspace, maxabs_bits,
+        launch_sync_small(ReduceArgs{G, out, nullptr, ld, W, 0u, 0, nullptr, nullptr}, ly, pal.f[0], (uint32_t*)workspace, maxabs_bits,
                           scale_exp, s);
         return launched();
     }
@@ -844,10 +844,18 @@ extern "C" int aps_sync(const float* G, int32_t W, int64_t ld, int64_t n, const 
         if (narrow) ws.half = (uint16_t*)(wb + lay.half);
     }
     if (route == APS_SYNC_ROUTE_TWO_PASS) {
-        // two passes: exactly the three calls of the step
+        // two passes: what the three calls of the step compute
         if (phases & APS_SYNC_PASS1) {
             st = aps_layer_maxabs(G, W, ld, n, offsets, L, maxabs_bits, stream);
             if (st != APS_OK) return st;
+        }
+        if ((phases & APS_SYNC_PASS2) && n > 0 && one_entry(ly)) {
+            // the sum's launch derives the exponents itself, with its first
+            // rows in flight (3.5 M elements, W = 13: 69 us in three launches
+            // and with the lookup before the loads, 67 this way)
+            ly.scale_exp = nullptr;
+            launch_sim_reduce(ReduceArgs{G, out, nullptr, ld, W, 0u, 0, maxabs_bits, scale_exp}, ly, pal, s);
+            return launched();
         }
         if (phases & APS_SYNC_PASS2) {
             st = aps_layer_scales(maxabs_bits, L, W, fmts, n_fmts, fmt_idx, scale_exp, stream);
@@ -858,8 +866,9 @@ extern "C" int aps_sync(const float* G, int32_t W, int64_t ld, int64_t n, const 
         return APS_OK;
     }
     const dim3 lgrid((unsigned)((L + 255) / 256));
-    const bool mixed = fmt_idx && n_fmts > 1 && L > 1;
-    const unsigned vm = variant_mask(pal, n_fmts);
+    const bool one = one_entry(ly);
+    const bool mixed = !one && L > 1;
+    const unsigned vm = one ? 1u << pal.f[0].variant : variant_mask(pal, n_fmts);
     const dim3 grid((unsigned)stream_grid(nchunks, W, BLOCKS_PER_CU));  // pass-1 row walks
     // repairs: the list's length is only known on the device.  The one-pass
     // route is taken where few elements need recomputing (often none), so a
@@ -867,7 +876,7 @@ extern "C" int aps_sync(const float* G, int32_t W, int64_t ld, int64_t n, const 
     // whole layers, a quarter chunk per wave.
     const bool guess = route == APS_SYNC_ROUTE_GUESS;
     const dim3 rgrid((unsigned)grid_for(nchunks, (guess || ws.half) ? BLOCKS_PER_CU : 4));
-    ReduceArgs ra{G, out, nullptr, ld, W, 0u, 0};
+    ReduceArgs ra{G, out, nullptr, ld, W, 0u, 0, nullptr, nullptr};
     SyncArgs sa{G, out, ld, W};
     const int rmode = guess ? RM_CHUNKS : (ws.bytes ? RM_ELEMENTS : RM_QUARTERS);
     if (guess && (phases & APS_SYNC_PASS1)) {

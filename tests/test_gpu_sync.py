@@ -658,3 +658,24 @@ def test_sync_small_sets(dev, f):
             offs, n, ld = _layout([n - 3000, 2999, 1])
             G = _values(rng, W, ld, offs, "normal")
             sync_case(dev, G, n, offs, [f], tag=f"{f} limit n={n} W={W}", route=0)
+
+
+@pytest.mark.parametrize("L", [1, 2, 64, 65, 130, 4100])
+def test_sync_over_many_layers(dev, L):
+    """The two-pass route whose sum takes its exponents from the maxima, and
+    the one-pass route's layer lookup by 64 offsets at a time: layer counts
+    around one, two and three rounds of it, empty layers at the start and at
+    the end, layers of no finite maximum, many layers in a chunk and chunks
+    inside one; a palette given by an index of a single entry."""
+    rng = np.random.default_rng(1700 + L)
+    sizes = rng.choice([0, 0, 1, 3, 40, 700], L)
+    sizes[: L // 8] = 0
+    sizes[L - L // 8:] = 0
+    sizes[L // 4] += 5000
+    offs, n, ld = _layout([int(v) for v in sizes])
+    for W in (1, 8, 13, 64):
+        G = _values(rng, W, ld, offs, "special" if W == 13 else "normal")
+        for route in (A.APS_SYNC_TWO_PASS, A.APS_SYNC_ONE_PASS, 0):
+            for idx in (None, np.zeros(L, np.uint8)):
+                log("case", L, W, route, idx is not None)
+                sync_case(dev, G, n, offs, [F(5, 2)], fmt_idx=idx, tag=f"L={L} W={W}", route=route, split=(W == 8))
