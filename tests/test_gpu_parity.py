@@ -1008,3 +1008,34 @@ def test_layer_lookup_over_many_layers(dev, L):
     run_case(dev, G, n, offs, [F(5, 2)], mode="aps", tag=f"L={L} n={n}")
     idx = (rng.random(L) < 0.25).astype(np.uint8)
     run_case(dev, G, n, offs, [F(5, 2), F(4, 3)], fmt_idx=idx, mode="aps", tag=f"L={L} n={n} two formats")
+
+
+@pytest.mark.parametrize("acc", [A.APS_ACC_SEQUENTIAL, A.APS_ACC_KAHAN])
+@pytest.mark.parametrize("f", [F(5, 2), F(5, 10), F(5, 2, 14)], ids=str)
+def test_ordered_reduce_by_hardware_chains(dev, f, acc):
+    """The summation orders of the formats whose chains run on the hardware's
+    conversions (and of one of the same widths with another bias, whose do
+    not): INF, NaN, subnormals and sums that cross the overflow threshold,
+    ring segments of less than a chunk, of one and of several, group sizes 1,
+    W and between, each flag, and a palette whose chunks take different forms."""
+    bias = ofmt(f).b
+    rng = np.random.default_rng(1600 + f.m + bias + 100 * acc)
+    offs, n, ld = _layout([1024, 2048 + 5, 0, 1019, 3072, 700, 1, 3071])
+    idx = np.array([0, 1, 0, 1, 0, 2, 2, 1], np.uint8)
+    for W, k in ((1, 1), (2, 1), (6, 2), (16, 16), (24, 8), (64, 1)):
+        G = _values(rng, W, ld, offs, "normal" if W == 6 else "special")
+        top = 2.0 ** (2 ** f.e - 2 - bias)
+        G[:, ::7] = (rng.uniform(-2, 2, (W, (ld + 6) // 7)) * top).astype(np.float32)          # overflow and cancellation
+        G[:, 3::7] = (rng.uniform(-9, 9, (W, (ld + 3) // 7)) * 2.0 ** (1 - bias - f.m)).astype(np.float32)  # subnormals
+        G[:, n:] = 7.0
+        se = rng.integers(-3, 4, offs.size - 1).astype(np.int32)
+        for flags in (0, A.APS_OUTPUT_SCALED):
+            for pal, ix in (([f], None), ([f, F(4, 3), F(5, 10)], idx)):
+                log(f"hardware chains {f} W={W} k={k} acc={acc} flags={flags} palette of {len(pal)}")
+                out = torch.full((n,), float("nan"), device=dev)
+                A.aps_sim_reduce_ex(torch.from_numpy(G).to(dev), n, torch.from_numpy(offs).to(dev),
+                                    torch.from_numpy(se).to(dev), pal, None if ix is None else torch.from_numpy(ix).to(dev),
+                                    flags, group=k, accumulator=acc, out=out)
+                ref = O.sim_reduce_ex(G, n, offs, se, [ofmt(p) for p in pal], ix, flags=flags, group=k, accumulator=acc)
+                g = out.cpu().numpy()
+                assert same_f32(g, ref), first_diff(g, ref)
