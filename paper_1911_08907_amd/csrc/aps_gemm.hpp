@@ -172,12 +172,16 @@ struct GemmTile {
     static constexpr int RB = BLOCK / TPB;   // rows of B between a thread's loads
 };
 
-// A thread's loads of A and B, one k-tile at a time.  Every k-tile but the
-// last is read by unconditional 16-byte loads: rows of A past the last one
-// read the last, and columns of B past the last one whatever follows in the
-// matrix (such outputs are not stored; only B's last row could end before
-// such a load does, and it belongs to the last k-tile).  The last k-tile is
-// read element by element with the indices clamped.
+// A thread's loads of A and B, one k-tile at a time.  Every k-tile that ends
+// three or more k before the last is read by unconditional 16-byte loads:
+// rows of A past the last one read the last, and columns of B past the last
+// one whatever follows in the matrix (such outputs are not stored), by offsets
+// held to B's last four elements.  No column of B is held back so: in its
+// first K-3 rows the four from column b (a multiple of 4 below N) start no
+// later than (K-4) ldb + b <= (K-1) ldb + N-4, since b+4-N <= 3 <= 3 ldb.  One
+// row more would not do for N = 1 and ldb < 3.  The last k-tile, and the one
+// before it where the last holds one or two k, are read element by element
+// with the indices clamped.
 template <class D>
 struct GemmLoads {
     const float* pa[D::FA];
@@ -194,7 +198,7 @@ struct GemmLoads {
     }
     // the k-tile from k0 on; tiles are fetched in order
     __device__ __forceinline__ void fetch(const GemmArgs& g, int k0, int64_t n0) {
-        if (k0 + D::GK < g.K) {
+        if (k0 + D::GK + 2 < g.K) {
 #pragma unroll
             for (int r = 0; r < D::FA; ++r) {
                 ra[r] = *(const f4u*)pa[r];
@@ -209,9 +213,11 @@ struct GemmLoads {
         pin(t);  // keeps this path's addresses out of the registers of the k loop
         const int k = k0 + t % D::TPA * 4;
 #pragma unroll
-        for (int r = 0; r < D::FA; ++r)
+        for (int r = 0; r < D::FA; ++r) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) ra[r][q] = pa[r][min(k + q, g.K - 1) - k];
+            pa[r] += D::GK;
+        }
 #pragma unroll
         for (int r = 0; r < D::FB; ++r) {
             const float* row = g.B + min(k0 + t / D::TPB + r * D::RB, g.K - 1) * g.ldb;

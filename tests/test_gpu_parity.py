@@ -918,6 +918,27 @@ def test_lp_gemm_fused_products_and_small_tiles(dev, fin, facc, acc):
             assert bool((c.as_strided((M, 1), (N + 1, 1), c.storage_offset() + N) == 7.0).all())
 
 
+@pytest.mark.parametrize("acc", [A.APS_ACC_SEQUENTIAL, A.APS_ACC_KAHAN])
+@pytest.mark.parametrize("fin,facc", [(F(5, 2), F(5, 10)), (F(4, 3), F(8, 7)), (F(5, 2), F(8, 23))], ids=str)
+def test_lp_gemm_narrow_b_rows(dev, fin, facc, acc):
+    # B's rows shorter than a 16-byte load, one after the other or nearly so
+    # (ldb = 1, 2): the whole of B's end lies within one load of the k-tile
+    # before the last; K one to four beyond the k-tiles of 16, 32 and 64
+    rng = np.random.default_rng(1250 + facc.m + 31 * acc)
+    for M in (1, 40):
+        for N, ldb in ((1, 1), (1, 2), (2, 2), (3, 3)):
+            for K in [t + r for t in (16, 32, 64, 128) for r in (1, 2, 3, 4)]:
+                Am, Bm = _gemm_inputs(rng, M, N, K, fin, False)
+                log(f"lp_gemm narrow {fin}->{facc} acc={acc} M={M} N={N} K={K} ldb={ldb}")
+                b = torch.zeros((K, ldb), device=dev)[:, :N]
+                b.copy_(torch.from_numpy(Bm))
+                got = A.aps_lp_gemm(torch.from_numpy(Am).to(dev), b, fin, facc, acc)
+                torch.cuda.synchronize()
+                ref = O.lp_gemm(Am, Bm, ofmt(fin), ofmt(facc), acc)
+                g = got.cpu().numpy()
+                assert same_f32(g, ref), (fin, facc, acc, M, N, K, ldb, first_diff(g, ref))
+
+
 @pytest.mark.parametrize("M,N,fin,facc,acc", [
     (3585, 3455, F(5, 2), F(5, 10), 0),   # half, 8 x 8 outputs per thread
     (2047, 1930, F(5, 2), F(5, 10), 0),   # 8 x 4
