@@ -190,7 +190,7 @@ __host__ __device__ __forceinline__ int hw_of_chain(const FmtK& f) { return f.hw
 
 // Chunks of one palette entry that cross ring segments, one block per
 // segment boundary (the block of the first boundary inside a chunk owns it):
-// one row walk per segment the chunk touches; after each, the elements of
+// one row walk per segment with an element in the chunk; after each, the elements of
 // that segment are stored at once (a thread owns both nibbles of its code
 // bytes, so the read-modify-writes of a byte split between segments come in
 // program order).
@@ -215,8 +215,10 @@ __device__ void reduce_cross(const ReduceArgs& a, const Layers& ly, const Pal& p
     } else {
         elem_scales(ly, ci, j, ft);
     }
-    const int64_t seg_last = ring_segment(end - 1, ly.n, od.ng);
-    for (int64_t sg = ring_segment(start, ly.n, od.ng); sg <= seg_last; ++sg) {
+    // segments without an element (more segments than elements) take no walk:
+    // the next one is that of the first element not yet stored
+    for (int64_t at = start; at < end;) {
+        const int64_t sg = ring_segment(at, ly.n, od.ng);
         PendingOut part;
         part.valid = false;
         reduce_vec_ex<V, HW, KAHAN>(a, f, j, end, ft, (int)sg, od, part);
@@ -238,6 +240,7 @@ __device__ void reduce_cross(const ReduceArgs& a, const Layers& ly, const Pal& p
                 }
             }
         }
+        at = hi;
     }
 }
 

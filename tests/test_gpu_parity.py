@@ -600,6 +600,25 @@ def test_ordered_reduce_w256_groups(dev):
         _run_ex(dev, G, n, offs, [F(5, 2)], None, se, k, A.APS_ACC_SEQUENTIAL, f"W=256 k={k}")
 
 
+@pytest.mark.parametrize("acc", [A.APS_ACC_SEQUENTIAL, A.APS_ACC_KAHAN])
+def test_ordered_reduce_more_segments_than_elements(dev, acc):
+    """More ring segments than elements: most segments are empty, and only
+    those with an element are walked (one walk of the 2^16 rows per element
+    takes milliseconds, one per segment would take a quarter of an hour).
+    Also a whole chunk and a ragged one of single-element segments."""
+    rng = np.random.default_rng(90 + acc)
+    for W, k, offs in ((1 << 16, 1, [0, 2, 5]), (1 << 14, 4, [0, 2, 5]), (2048, 1, [0, 7, 1030])):
+        offs = np.array(offs, np.int64)
+        n = int(offs[-1])
+        ld = (n + 7) // 8 * 8
+        G = (rng.standard_normal((W, ld)) * 1e-2).astype(np.float32)
+        G[:, n:] = np.nan
+        for f in (F(5, 2), F(3, 0)):
+            se = O.layer_scales(O.layer_maxabs(G, n, offs), W, ofmt(f))
+            log("W", W, "k", k, f)
+            _run_ex(dev, G, n, offs, [f], None, se, k, acc, f"{f} W={W} k={k} n={n}")
+
+
 # ------------------------------- low-precision-accumulator GEMM (Sec. 5, CPD)
 
 # (input format, accumulator format): every accumulator variant of the kernel
