@@ -188,19 +188,31 @@ __device__ __forceinline__ int64_t ring_segment(int64_t j, int64_t n, int ng) { 
 // The hardware form of an entry's chains.
 __host__ __device__ __forceinline__ int hw_of_chain(const FmtK& f) { return f.hw == HW_E4M3 ? HW_NONE : f.hw; }
 
-// Chunks of one palette entry that cross ring segments, one block per
-// segment boundary (the block of the first boundary inside a chunk owns it):
-// one row walk per segment with an element in the chunk; after each, the elements of
-// that segment are stored at once (a thread owns both nibbles of its code
-// bytes, so the read-modify-writes of a byte split between segments come in
-// program order).
+// The chunk that cross block b of ncross takes, or -1: with fewer segment
+// boundaries than chunks one block per boundary (that of the first boundary
+// inside a chunk owns it), else one per chunk.
+__device__ __forceinline__ int64_t cross_chunk(int b, int ncross, int64_t n, const Order& od) {
+    if (ncross < od.ng - 1) {
+        const int64_t start = (int64_t)b * CH;
+        return ring_segment(start, n, od.ng) != ring_segment(min(start + CH, n) - 1, n, od.ng) ? b : -1;
+    }
+    const int64_t s1 = (int64_t)b + 1;  // boundary: first element of segment s1
+    const int64_t p = (s1 * n + od.ng - 1) / od.ng;
+    if (p <= 0 || p >= n || p % CH == 0) return -1;  // at a chunk edge: nothing crosses
+    if (s1 > 1 && ((s1 - 1) * n + od.ng - 1) / od.ng > p / CH * CH) return -1;  // an earlier boundary owns it
+    return p / CH;
+}
+
+// Chunks of one palette entry that cross ring segments, one block each:
+// one row walk per segment with an element in the chunk; after each, the
+// elements of that segment are stored at once (a thread owns both nibbles of
+// its code bytes, so the read-modify-writes of a byte split between segments
+// come in program order).
 template <int V, int HW, bool KAHAN>
-__device__ void reduce_cross(const ReduceArgs& a, const Layers& ly, const Pal& pal, const Order& od, int boundary) {
-    const int64_t s1 = (int64_t)boundary + 1;                  // boundary: first element of segment s1
-    const int64_t p = (s1 * ly.n + od.ng - 1) / od.ng;
-    if (p <= 0 || p >= ly.n || p % CH == 0) return;           // at a chunk edge: nothing crosses
-    const int64_t start = p / CH * CH;
-    if (s1 > 1 && ((s1 - 1) * ly.n + od.ng - 1) / od.ng > start) return;  // an earlier boundary owns it
+__device__ void reduce_cross(const ReduceArgs& a, const Layers& ly, const Pal& pal, const Order& od, int b, int ncross) {
+    const int64_t c = cross_chunk(b, ncross, ly.n, od);
+    if (c < 0) return;
+    const int64_t start = c * CH;
     const int64_t end = min(start + CH, ly.n);
     const ChunkInfo ci = chunk_layers(ly, start, end);
     if (ci.mixed) return;  // k_sim_reduce_ex_slow
@@ -251,7 +263,7 @@ __device__ void reduce_cross(const ReduceArgs& a, const Layers& ly, const Pal& p
 template <int V, int HW, bool KAHAN>
 __global__ __launch_bounds__(BLOCK, 4) void k_sim_reduce_ex(ReduceArgs a, Layers ly, Pal pal, Order od, int ncross) {
     if ((int)blockIdx.x < ncross) {
-        reduce_cross<V, HW, KAHAN>(a, ly, pal, od, blockIdx.x);
+        reduce_cross<V, HW, KAHAN>(a, ly, pal, od, blockIdx.x, ncross);
         return;
     }
     const int64_t nchunks = (ly.n + CH - 1) / CH;
@@ -395,7 +407,10 @@ extern "C" int aps_sim_reduce_ex(const float* G, int32_t W, int64_t ld, int64_t 
         if (hw) hm |= 1u << hw;
         else vm |= 1u << pal.f[i].variant;
     }
-    const int ncross = od.ng - 1;  // ring-segment boundaries
+    // as many blocks as chunks can cross ring segments (the number of
+    // boundaries alone would take the grid past its limit of 2^32 threads at
+    // W = 2^24)
+    const int ncross = (int)std::min<int64_t>(od.ng - 1, nchunks);
     const dim3 grid((unsigned)(grid_for(nchunks, BLOCKS_PER_CU) + ncross));
 #define APS_X(v, h)                                                                                          \
     if (acc == APS_ACC_KAHAN)                                                                                \

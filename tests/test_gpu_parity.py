@@ -619,6 +619,22 @@ def test_ordered_reduce_more_segments_than_elements(dev, acc):
             _run_ex(dev, G, n, offs, [f], None, se, k, acc, f"{f} W={W} k={k} n={n}")
 
 
+@pytest.mark.parametrize("acc", [A.APS_ACC_SEQUENTIAL, A.APS_ACC_KAHAN])
+@pytest.mark.parametrize("n", [1, 2])
+def test_ordered_reduce_maximum_workers(dev, n, acc):
+    """APS_MAX_WORKERS in one ring: 2^24 - 1 segment boundaries, of which a
+    gradient of one chunk crosses at most one block's worth.  One element is
+    one walk of the plain kind, two are a walk per segment."""
+    W, ld = 1 << 24, 4
+    offs = np.array([0, n], np.int64)
+    rng = np.random.default_rng(95 + n)
+    G = rng.standard_normal((W, ld), dtype=np.float32) * np.float32(1e-2)
+    G[:, n:] = np.nan
+    se = O.layer_scales(O.layer_maxabs(G, n, offs), W, O.Format(5, 2))
+    log("n", n, "acc", acc)
+    _run_ex(dev, G, n, offs, [F(5, 2)], None, se, 1, acc, f"n={n} acc={acc}")
+
+
 # ------------------------------- low-precision-accumulator GEMM (Sec. 5, CPD)
 
 # (input format, accumulator format): every accumulator variant of the kernel
