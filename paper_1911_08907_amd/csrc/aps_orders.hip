@@ -31,12 +31,12 @@ __device__ __forceinline__ int order_row(int r, int seg, const Order& od) {
 template <int V, int HW, bool KAHAN>
 struct Chain4 {
     float s[4], c[4];
-    bool bad[4];
     __device__ __forceinline__ static int domain(const FmtK& f) { return HW == HW_NONE ? f.k : 0; }
-    __device__ __forceinline__ void cast(const f4& x, const int F[4], const FmtK& f, float q[4]) {
+    __device__ __forceinline__ void cast(const f4& x, const int F[4], const FmtK& f, float q[4],
+                                                bool (&flag)[4]) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if constexpr (HW == HW_NONE) q[e] = quant<V>(x[e], F[e], f, bad[e]);
+            if constexpr (HW == HW_NONE) q[e] = quant<V>(x[e], F[e], f, flag[e]);
             else q[e] = __builtin_amdgcn_ldexpf(x[e], F[e]);
         }
         if constexpr (HW == HW_E5M2) {
@@ -52,7 +52,7 @@ struct Chain4 {
             c[e] = 0.0f;
         }
     }
-    // q joins the chain; `bad` as in chain_step
+    // q joins the chain; `flag` as chain_step's `bad`
     __device__ __forceinline__ void add(const float q[4], const FmtK& f, bool (&flag)[4]) {
         if constexpr (HW == HW_E5M2) {
 #pragma unroll
@@ -80,9 +80,8 @@ struct Chain4 {
 template <int V, bool KAHAN>
 struct Chain4<V, HW_HALF, KAHAN> {
     h2 s[2], c[2];
-    bool bad[4];
     __device__ __forceinline__ static int domain(const FmtK&) { return 0; }
-    __device__ __forceinline__ void cast(const f4& x, const int F[4], const FmtK&, h2 q[2]) {
+    __device__ __forceinline__ void cast(const f4& x, const int F[4], const FmtK&, h2 q[2], bool (&)[4]) {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
             q[h] = h2{(_Float16)__builtin_amdgcn_ldexpf(x[2 * h], F[2 * h]),
@@ -126,8 +125,6 @@ __device__ __forceinline__ void reduce_vec_ex(const ReduceArgs& a, const FmtK& f
     }
     C S, T;  // the group's chain, the ring's
     bool bad[4] = {false, false, false, false};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) S.bad[e] = false;
     const float* p = a.G + j;
     const int64_t ld = a.ld;
     const int kg = 1 << od.log2k;
@@ -139,7 +136,7 @@ __device__ __forceinline__ void reduce_vec_ex(const ReduceArgs& a, const FmtK& f
         a.W, [&](int rr) { return ld4(p + (int64_t)order_row(rr, seg, od) * ld); }, [&]() { flush_out(a, pd); },
         [&](const f4& x) {
             Q q;
-            S.cast(x, F, f, q);
+            S.cast(x, F, f, q, bad);
             S.start(q);  // master of the first group
             zero(q);
             T.start(q);
@@ -147,7 +144,7 @@ __device__ __forceinline__ void reduce_vec_ex(const ReduceArgs& a, const FmtK& f
         [&](const f4& x, bool valid) {
             if (valid) {
                 Q q;
-                S.cast(x, F, f, q);
+                S.cast(x, F, f, q, bad);
                 if ((r & (kg - 1)) == 0) {
                     // a new group starts: fold the finished group sum into the ring
                     if (r == kg) T.start(S.s);
@@ -168,7 +165,7 @@ __device__ __forceinline__ void reduce_vec_ex(const ReduceArgs& a, const FmtK& f
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         if constexpr (HW == HW_HALF) s[e] = (float)T.s[e >> 1][e & 1];
-        else s[e] = finish<V>(T.s[e], bad[e] || S.bad[e]);
+        else s[e] = finish<V>(T.s[e], bad[e]);
     }
     pd.o.x = __builtin_amdgcn_ldexpf(s[0], Fo[0]);
     pd.o.y = __builtin_amdgcn_ldexpf(s[1], Fo[1]);
@@ -188,33 +185,68 @@ __device__ __forceinline__ int64_t ring_segment(int64_t j, int64_t n, int ng) { 
 // The hardware form of an entry's chains.
 __host__ __device__ __forceinline__ int hw_of_chain(const FmtK& f) { return f.hw == HW_E4M3 ? HW_NONE : f.hw; }
 
-// The chunk that cross block b of ncross takes, or -1: with fewer segment
-// boundaries than chunks one block per boundary (that of the first boundary
-// inside a chunk owns it), else one per chunk.
-__device__ __forceinline__ int64_t cross_chunk(int b, int ncross, int64_t n, const Order& od) {
+// Elements from `at` on up to the end of their ring segment.
+struct Span {
+    int64_t at, hi;
+    int seg;
+};
+
+// Segment seg holds the elements i with floor(i * ng / n) = seg.
+__device__ __forceinline__ int64_t segment_end(int seg, int64_t n, int ng) { return ((seg + (int64_t)1) * n + ng - 1) / ng; }
+
+// The chunk that cross block b of ncross takes and its first segment's part
+// (from the chunk's start on), or false: with fewer segment boundaries than
+// chunks one block per boundary (that of the first boundary inside a chunk
+// owns it), else one per chunk.
+__device__ __forceinline__ bool cross_chunk(int b, int ncross, int64_t n, const Order& od, int64_t& c, Span& sp) {
     if (ncross < od.ng - 1) {
-        const int64_t start = (int64_t)b * CH;
-        return ring_segment(start, n, od.ng) != ring_segment(min(start + CH, n) - 1, n, od.ng) ? b : -1;
+        c = b;
+        sp.at = c * CH;
+        sp.seg = (int)ring_segment(sp.at, n, od.ng);
+        sp.hi = segment_end(sp.seg, n, od.ng);
+        return sp.hi < min(sp.at + CH, n);
     }
-    const int64_t s1 = (int64_t)b + 1;  // boundary: first element of segment s1
-    const int64_t p = (s1 * n + od.ng - 1) / od.ng;
-    if (p <= 0 || p >= n || p % CH == 0) return -1;  // at a chunk edge: nothing crosses
-    if (s1 > 1 && ((s1 - 1) * n + od.ng - 1) / od.ng > p / CH * CH) return -1;  // an earlier boundary owns it
-    return p / CH;
+    sp.seg = b;
+    sp.hi = segment_end(b, n, od.ng);  // boundary: first element of segment b + 1
+    c = sp.hi / CH;
+    sp.at = c * CH;
+    if (sp.hi >= n || sp.hi == sp.at) return false;                // at a chunk edge: nothing crosses
+    return b == 0 || segment_end(b - 1, n, od.ng) <= sp.at;  // else an earlier boundary owns it
 }
 
-// Chunks of one palette entry that cross ring segments, one block each:
-// one row walk per segment with an element in the chunk; after each, the
-// elements of that segment are stored at once (a thread owns both nibbles of
-// its code bytes, so the read-modify-writes of a byte split between segments
-// come in program order).
-template <int V, int HW, bool KAHAN>
-__device__ void reduce_cross(const ReduceArgs& a, const Layers& ly, const Pal& pal, const Order& od, int b, int ncross) {
-    const int64_t c = cross_chunk(b, ncross, ly.n, od);
-    if (c < 0) return;
+// Stores those of a thread's 4 finished outputs that lie in [lo, hi).  A
+// thread owns both nibbles of its code bytes, so the read-modify-writes of a
+// byte split between segments come in program order.
+__device__ __forceinline__ void store_part(const ReduceArgs& a, const PendingOut& pd, int64_t lo, int64_t hi) {
+    const float o[4] = {pd.o.x, pd.o.y, pd.o.z, pd.o.w};
+    int32_t j = (int32_t)pd.j;  // addresses from here on, not held over the walk (25 registers)
+    asm volatile("" : "+v"(j));
+    for (int e = 0; e < 4; ++e) {
+        const int64_t jj = (int64_t)j + e;
+        if (jj < lo || jj >= hi) continue;
+        if (a.out) a.out[jj] = o[e];
+        if (!a.codes) continue;
+        if (a.code_cls == 0) {
+            uint8_t* pb = a.codes + (jj >> 1);
+            *pb = (jj & 1) ? (uint8_t)((*pb & 0x0Fu) | ((pd.c[e] & 15u) << 4)) : (uint8_t)((*pb & 0xF0u) | (pd.c[e] & 15u));
+        } else {
+            put_code(a.codes, jj, pd.c[e], a.code_cls);
+        }
+    }
+}
+
+// Which chunks a copy of the walk below takes.
+enum ExChunks { EX_WHOLE = 0, EX_CROSS = 1, EX_BOTH = 2 };
+
+// Chunk c: a walk of the rows, or where it crosses ring segments (sp: its
+// first segment's part) one per segment with an element in the chunk, whose
+// elements are stored after it.
+template <int V, int HW, bool KAHAN, int WHICH>
+__device__ __forceinline__ void ex_chunk(const ReduceArgs& a, const Layers& ly, const Pal& pal, const Order& od, int64_t c,
+                                         Span sp, LayerCur& cur, PendingOut& pd) {
     const int64_t start = c * CH;
     const int64_t end = min(start + CH, ly.n);
-    const ChunkInfo ci = chunk_layers(ly, start, end);
+    const ChunkInfo ci = chunk_layers(ly, start, end, cur);
     if (ci.mixed) return;  // k_sim_reduce_ex_slow
     const FmtK& f = pal.f[ci.pidx];
     if (f.variant != V || hw_of_chain(f) != HW) return;
@@ -227,71 +259,77 @@ __device__ void reduce_cross(const ReduceArgs& a, const Layers& ly, const Pal& p
     } else {
         elem_scales(ly, ci, j, ft);
     }
-    // segments without an element (more segments than elements) take no walk:
-    // the next one is that of the first element not yet stored
-    for (int64_t at = start; at < end;) {
-        const int64_t sg = ring_segment(at, ly.n, od.ng);
-        PendingOut part;
-        part.valid = false;
-        reduce_vec_ex<V, HW, KAHAN>(a, f, j, end, ft, (int)sg, od, part);
-        // segment sg holds the elements i with floor(i * ng / n) = sg
-        const int64_t lo = (sg * ly.n + od.ng - 1) / od.ng;
-        const int64_t hi = min(((sg + 1) * ly.n + od.ng - 1) / od.ng, end);
-        const float po[4] = {part.o.x, part.o.y, part.o.z, part.o.w};
-        for (int e = 0; e < 4; ++e) {
-            const int64_t jj = j + e;
-            if (jj < lo || jj >= hi) continue;
-            if (a.out) a.out[jj] = po[e];
-            if (a.codes) {
-                if (a.code_cls == 0) {
-                    uint8_t* pb = a.codes + (jj >> 1);
-                    *pb = (jj & 1) ? (uint8_t)((*pb & 0x0Fu) | ((part.c[e] & 15u) << 4))
-                                   : (uint8_t)((*pb & 0xF0u) | (part.c[e] & 15u));
-                } else {
-                    put_code(a.codes, jj, part.c[e], a.code_cls);
-                }
-            }
-        }
-        at = hi;
+    if constexpr (WHICH == EX_WHOLE) {
+        reduce_vec_ex<V, HW, KAHAN>(a, f, j, end, ft, sp.seg, od, pd);
+        return;
+    }
+    for (;;) {
+        reduce_vec_ex<V, HW, KAHAN>(a, f, j, end, ft, sp.seg, od, pd);
+        if (sp.at == start && sp.hi >= end) return;  // a whole chunk
+        store_part(a, pd, sp.at, min(sp.hi, end));
+        pd.valid = false;
+        if (sp.hi >= end) return;
+        // segments without an element (more segments than elements) take no
+        // walk: the next one is that of the first element not yet stored
+        sp.at = sp.hi;
+        sp.seg = od.ng <= ly.n ? sp.seg + 1 : (int)ring_segment(sp.at, ly.n, od.ng);
+        sp.hi = segment_end(sp.seg, ly.n, od.ng);
     }
 }
 
-// The first `ncross` blocks take the chunks that cross ring segments
-// (reduce_cross), so that their lone walks, two per chunk and bound by
-// latency, run beside the others instead of after them (ResNet-50 W = 64: 45
-// us of 1190).  At most 128 registers: four waves per SIMD.
-template <int V, int HW, bool KAHAN>
-__global__ __launch_bounds__(BLOCK, 4) void k_sim_reduce_ex(ReduceArgs a, Layers ly, Pal pal, Order od, int ncross) {
-    if ((int)blockIdx.x < ncross) {
-        reduce_cross<V, HW, KAHAN>(a, ly, pal, od, blockIdx.x, ncross);
-        return;
-    }
-    const int64_t nchunks = (ly.n + CH - 1) / CH;
-    const int64_t nb = (int64_t)gridDim.x - ncross, b = (int64_t)blockIdx.x - ncross;
-    const int64_t cb = nchunks * b / nb, ce = nchunks * (b + 1) / nb;
+constexpr bool ex_m0(int V) { return V == V_INT_M0 || V == V_TOP_M0 || V == V_LOW_M0; }
+
+// Waves per SIMD asked of an instance: four (at most 128 registers) where that
+// costs no scratch or little: 1-5-2 and the fp32 chains fit, wide Kahan chains
+// (fp64 adds) beside a crossing copy spill 17 registers and gain all the same.
+// Without a crossing copy those are left to the compiler (134 to 137 registers),
+// as are Kahan's m = 0 chains (152 to 154), three waves each: held to 128 the
+// latter spill 46, in the row walk too.
+constexpr int ex_waves(int V, bool KAHAN, bool CROSS) {
+    const bool wide = V == V_INT_F64 || V == V_TOP_F64 || V == V_LOW_F64 || V == V_GEN;
+    return KAHAN && (ex_m0(V) || (wide && !CROSS)) ? 1 : 4;
+}
+
+// CROSS: the first `ncross` blocks take the chunks that cross ring segments,
+// one each, whose lone walks, two or more per chunk and bound by latency, so
+// run beside the other blocks' instead of after them (ResNet-50 W = 64: 45 us
+// of 1190).  They have a copy of the walk to themselves, so that the other
+// blocks' keeps its registers, but for Kahan's m = 0 chains, where one copy
+// serves both.  Measured on MI355X, us, a launch of the crossing chunks after
+// the others and this one: ResNet-50 W = 64 k = 16 Kahan 1-5-2 1216 and 1160,
+// 1-3-0 1349 and 1260; W = 8 k = 2 plain 187 and 175 to 179; W = 2 ring plain
+// 1-3-0 98 and 87; ResNet-20 W = 8 ring 16 to 20 and 8 to 11.
+template <int V, int HW, bool KAHAN, bool CROSS>
+__global__ __launch_bounds__(BLOCK, ex_waves(V, KAHAN, CROSS)) void k_sim_reduce_ex(ReduceArgs a, Layers ly, Pal pal,
+                                                                                   Order od, int ncross) {
+    constexpr bool ONE = ex_m0(V) && KAHAN;
     LayerCur cur{-1, 0};
     PendingOut pd;
     pd.valid = false;
-    for (int64_t c = cb; c < ce; ++c) {
-        const int64_t start = c * CH;
-        const int64_t end = min(start + CH, ly.n);
-        const ChunkInfo ci = chunk_layers(ly, start, end, cur);
-        const int64_t seg = ring_segment(start, ly.n, od.ng);
-        // chunks that mix palette entries: k_sim_reduce_ex_slow; chunks that
-        // cross ring segments: reduce_cross
-        if (ci.mixed || seg != ring_segment(end - 1, ly.n, od.ng)) continue;
-        const FmtK& f = pal.f[ci.pidx];
-        if (f.variant != V || hw_of_chain(f) != HW) continue;
-        const int64_t j = start + (int64_t)threadIdx.x * VEC;
-        if (j >= end) continue;
-        int32_t ft[4];
-        if (ci.i0 == ci.i1) {
-            const int32_t t = ly.scale_exp ? clamp_exp(cld(ly.scale_exp, ci.i0)) : 0;
-            ft[0] = ft[1] = ft[2] = ft[3] = t;
-        } else {
-            elem_scales(ly, ci, j, ft);
+    const int64_t nchunks = (ly.n + CH - 1) / CH;
+    const int64_t nb = (int64_t)gridDim.x - ncross, b = (int64_t)blockIdx.x - ncross;
+    int64_t c, ce;
+    Span sp;
+    const bool cross = CROSS && b < 0;
+    if (cross) {
+        if (!cross_chunk(blockIdx.x, ncross, ly.n, od, c, sp)) return;
+        ce = c + 1;
+        if constexpr (!ONE) {
+            ex_chunk<V, HW, KAHAN, EX_CROSS>(a, ly, pal, od, c, sp, cur, pd);
+            return;
         }
-        reduce_vec_ex<V, HW, KAHAN>(a, f, j, end, ft, (int)seg, od, pd);
+    } else {
+        c = nchunks * b / nb;
+        ce = nchunks * (b + 1) / nb;
+    }
+    for (; c < ce; ++c) {
+        if (!cross) {
+            sp.at = c * CH;
+            sp.seg = (int)ring_segment(sp.at, ly.n, od.ng);
+            sp.hi = segment_end(sp.seg, ly.n, od.ng);
+            if (sp.hi < min(sp.at + CH, ly.n)) continue;  // crosses: one of the first blocks, or of a launch of its own
+        }
+        ex_chunk<V, HW, KAHAN, CROSS && ONE ? EX_BOTH : EX_WHOLE>(a, ly, pal, od, c, sp, cur, pd);
     }
     flush_out(a, pd);
 }
@@ -412,11 +450,14 @@ extern "C" int aps_sim_reduce_ex(const float* G, int32_t W, int64_t ld, int64_t 
     // W = 2^24)
     const int ncross = (int)std::min<int64_t>(od.ng - 1, nchunks);
     const dim3 grid((unsigned)(grid_for(nchunks, BLOCKS_PER_CU) + ncross));
-#define APS_X(v, h)                                                                                          \
-    if (acc == APS_ACC_KAHAN)                                                                                \
-        hipLaunchKernelGGL((k_sim_reduce_ex<v, h, true>), grid, dim3(BLOCK), 0, s, a, ly, pal, od, ncross);  \
-    else                                                                                                     \
-        hipLaunchKernelGGL((k_sim_reduce_ex<v, h, false>), grid, dim3(BLOCK), 0, s, a, ly, pal, od, ncross);
+#define APS_XL(v, h, kahan, cross) \
+    hipLaunchKernelGGL((k_sim_reduce_ex<v, h, kahan, cross>), grid, dim3(BLOCK), 0, s, a, ly, pal, od, ncross)
+#define APS_X(v, h)                                                      \
+    if (acc == APS_ACC_KAHAN) {                                          \
+        if (ncross) APS_XL(v, h, true, true); else APS_XL(v, h, true, false);   \
+    } else {                                                             \
+        if (ncross) APS_XL(v, h, false, true); else APS_XL(v, h, false, false); \
+    }
     if (hm & (1u << HW_E5M2)) { APS_X(V_TOP_F32, HW_E5M2) }
     if (hm & (1u << HW_HALF)) { APS_X(V_TOP_F32, HW_HALF) }
 #define APS_LAUNCH_X(v) \
@@ -424,6 +465,7 @@ extern "C" int aps_sim_reduce_ex(const float* G, int32_t W, int64_t ld, int64_t 
     APS_FOR_VARIANTS(APS_LAUNCH_X)
 #undef APS_LAUNCH_X
 #undef APS_X
+#undef APS_XL
     if (fmt_idx && n_fmts > 1 && L > 1) {  // chunks that mix palette entries
         if (acc == APS_ACC_KAHAN)
             hipLaunchKernelGGL(k_sim_reduce_ex_slow<true>, dim3((unsigned)nchunks), dim3(BLOCK), 0, s, a, ly, pal, od);
