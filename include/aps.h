@@ -200,7 +200,8 @@ uint64_t aps_sync_workspace_bytes(int64_t n, int32_t L);
  * Which route aps_sync takes for W workers, n elements, this palette and
  * these flags (only the route bits of flags matter): APS_SYNC_ROUTE_*, or a
  * negative status (W or n out of range, a bad palette, more than one route
- * bit).  Host-only.
+ * bit).  With no route bit a small set of one format may run as two launches
+ * of its own instead (aps_sync below, "Small sets").  Host-only.
  */
 int aps_sync_route(int32_t W, int64_t n, const aps_format* fmts, int32_t n_fmts, uint32_t flags);
 
@@ -244,11 +245,16 @@ int aps_sync_route(int32_t W, int64_t n, const aps_format* fmts, int32_t n_fmts,
  * layer has the same format).
  *
  * Small sets.  With both passes in one call, no route bit and one format (no
- * fmt_idx, or one palette entry), a set of at most 2^20 elements and 2^24
- * element-workers, which stays in the caches, runs as two launches whatever
- * route it would take: the maxima per 256 elements and layer, then the
- * exponents and the scaled sums.  aps_sync_route names the route that larger
- * sets, and separate passes, take with the same rule.
+ * fmt_idx, or one palette entry), sets that stay in the caches run as two
+ * launches where that was measured faster than their route: the maxima per
+ * 256 elements and layer, then the exponents and the scaled sums.  They are
+ * those of at most 2^20 elements, and at most 2^18 per layer on the mean,
+ * with, where the route below would be the one-pass one, W <= 64 and
+ * W * n <= 2^23 (W = 64: 2^22), and where it would be two passes, W <= 4096 and
+ * W * n <= 3 * 2^22; with max(4, W / 16) layers and more per 1024 elements,
+ * W * n <= 2^24 in both (two passes: W <= 4096).  aps_sync_route, which knows
+ * neither the layers nor the passes, names the route that such a set takes with
+ * a route bit or in separate passes.
  *
  * Route choice: APS_SYNC_TWO_PASS and APS_SYNC_GUESS force their routes;
  * APS_SYNC_ONE_PASS takes the one-pass route wherever it applies (else two

@@ -393,7 +393,9 @@ def aps_sync_workspace_bytes(n: int, L: int) -> int:
 
 def aps_sync_route(W: int, n: int, fmts, flags: int = 0) -> int:
     """The route aps_sync takes for W workers, n elements and this palette
-    (only the route bits of ``flags`` matter): one of APS_SYNC_ROUTE_*."""
+    (only the route bits of ``flags`` matter): one of APS_SYNC_ROUTE_*.  A
+    small set of one format, without a route bit and with both passes in one
+    call, may run as two launches of its own instead (see aps.h)."""
     pal, nf = _palette(fmts)
     st = lib().aps_sync_route(int(W), int(n), pal, nf, int(flags))
     if st < 0:

@@ -761,17 +761,6 @@ extern "C" uint64_t aps_sync_workspace_bytes(int64_t n, int32_t L) {
 // cost more than they save on smaller ones), else two passes.
 constexpr int64_t GUESS_MIN_WORK = (int64_t)1 << 26;
 
-// Sets up to this size, of one format and with no route asked for, take the
-// two launches of aps_small.hip instead of the route's four or more.  Their
-// second launch reads all of a layer's unit maxima in every unit, which grows
-// with n squared, and all rows a second time, from the caches.  Measured on
-// MI355X, us per call in a graph, the route's launches against these: MLP
-// W = 2 15.0 and 7.9, ResNet-20 W = 8 21.2 and 10.1, 1 M elements W = 8 28.2
-// and 18.6, W = 13 31.2 and 26.0, 0.3 M W = 40 29.5 and 23.6; beyond, 2 M
-// W = 8 40.0 and 39.9, 5 M W = 3 49.3 and 114, 0.1 M W = 256 53 and 63.
-constexpr int64_t SMALL_MAX_N = (int64_t)1 << 20;
-constexpr int64_t SMALL_MAX_WORK = (int64_t)1 << 24;
-
 static bool one_pass_applies(int32_t W, const Pal& pal, int32_t n_fmts) {
     if (W & (W - 1)) return false;
     for (int i = 0; i < n_fmts; ++i)
@@ -791,6 +780,38 @@ static int sync_route(int32_t W, int64_t n, const Pal& pal, int32_t n_fmts, uint
         if (2 * lw + pal.f[i].emin - pal.f[i].emax + 2 > -7) pays = false;
     if (pays) return APS_SYNC_ROUTE_ONE_PASS;
     return (int64_t)W * n >= GUESS_MIN_WORK ? APS_SYNC_ROUTE_GUESS : APS_SYNC_ROUTE_TWO_PASS;
+}
+
+// Whether a set of one format, with no route asked for, takes the two launches
+// of aps_small.hip instead of its route's.  They read the rows twice (the
+// second time from the caches), a wave walks its W rows alone both times, and
+// each unit of the second reads its layer's unit maxima, ever more of them as
+// layers grow (of which the host knows the mean).  The routes cost about 1.5 us
+// more for every layer that ends inside a chunk.  So: n at most 2^20, n / L at
+// most 2^18, and against
+//   the one-pass route, which walks the rows once: W at most 64 with W * n at
+//     most 2^23 (W = 64: 2^22), or max(4, W / 16) layers per chunk;
+//   two passes: W at most 4096 with W * n at most 3 * 2^22, or 2^24 with that
+//     many layers.
+// Measured on MI355X, us per call in a graph, the route's launches and these,
+// d: layers per chunk:
+//   one-pass, 1-5-2, L = 16: W = 2 n = 2^20 23 and 12; W = 8 n = 2^20 25 and 14;
+//     W = 32 n = 2^18 17.2 and 13.4, 2^19 22.9 and 26.6; W = 64 n = 2^16 18.6
+//     and 17.3, 2^18 22.7 and 25.2.  L = 1: W = 8 n = 2^20 23 and 26, W = 16
+//     n = 2^18 13.9 and 12.0, W = 64 n = 2^17 18.1 and 18.9.  n = 2^14: W = 128
+//     d = 1 28 and 28, d = 8 41 and 30; W = 256 d = 4 46 and 51, d = 16 63 and
+//     53; W = 512 d = 16 91 and 101, d = 32 111 and 101; W = 1024 d = 1 126 and
+//     204, d = 64 203 and 206
+//   two passes, 1-4-3, L = 16: W = 8 n = 2^20 25 and 13; W = 13 n = 2^20 30 and
+//     24; W = 256 n = 2^14 55 and 50; W = 4096 n = 2^11 815 and 814; W = 8192
+//     n = 2^10 1511 and 1703.  L = 200: W = 16 n = 2^20 27.5 and 28.8.  L = 1:
+//     W = 8 n = 2^20 23 and 25, W = 40 n = 2^17.7 18.0 and 18.1
+static bool small_set(int32_t W, int64_t n, int32_t L, int route) {
+    if (n > ((int64_t)1 << 20) || n > ((int64_t)L << 18)) return false;
+    const int64_t work = (int64_t)W * n, nchunks = (n + CH - 1) / CH;
+    const bool many = L >= nchunks * std::max(4, W / 16) && work <= ((int64_t)1 << 24);
+    if (route == APS_SYNC_ROUTE_ONE_PASS) return many || (W <= 64 && work <= ((int64_t)1 << (W > 32 ? 22 : 23)));
+    return W <= 4096 && (many || work <= ((int64_t)3 << 22));
 }
 
 static constexpr uint32_t ROUTE_BITS = APS_SYNC_ONE_PASS | APS_SYNC_TWO_PASS | APS_SYNC_GUESS;
@@ -832,8 +853,8 @@ extern "C" int aps_sync(const float* G, int32_t W, int64_t ld, int64_t n, const 
               (int32_t*)(wb + lay.list), nullptr, (int32_t*)(wb + lay.guess), wb + lay.listed, W >= SYNC_BYTES_MIN_W};
     Layers ly{offsets, fmt_idx, scale_exp, n, L, n_fmts};
     const int route = sync_route(W, n, pal, n_fmts, flags);
-    if (phases == (APS_SYNC_PASS1 | APS_SYNC_PASS2) && !(flags & ROUTE_BITS) && (n_fmts == 1 || !fmt_idx) &&
-        n <= SMALL_MAX_N && (int64_t)W * n <= SMALL_MAX_WORK) {
+    if (phases == (APS_SYNC_PASS1 | APS_SYNC_PASS2) && !(flags & ROUTE_BITS) && one_entry(ly) &&
+        small_set(W, n, L, route)) {
         launch_sync_small(ReduceArgs{G, out, nullptr, ld, W, 0u, 0, nullptr, nullptr}, ly, pal.f[0], (uint32_t*)workspace, maxabs_bits,
                           scale_exp, s);
         return launched();

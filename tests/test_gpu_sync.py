@@ -644,7 +644,8 @@ def test_sync_small_sets(dev, f):
     """The default call on sets of a few units of 256 elements (two launches):
     unit edges, layers inside a unit, over many units and empty ones at both
     ends, worker counts around the register sets, every kind of value; and
-    the two sides of the size limit."""
+    large sets of three layers (the rule's two sides:
+    test_sync_small_set_rule)."""
     rng = np.random.default_rng(zlib.crc32(f"small/{f}".encode()))
     layouts = [[1], [255, 2], [0, 0, 256, 0, 256, 0], [100, 1, 155, 257, 3, 0, 1000], [7] * 80, [1] * 300 + [5000] + [2] * 9]
     for sizes in layouts:
@@ -679,3 +680,36 @@ def test_sync_over_many_layers(dev, L):
             for idx in (None, np.zeros(L, np.uint8)):
                 log("case", L, W, route, idx is not None)
                 sync_case(dev, G, n, offs, [F(5, 2)], fmt_idx=idx, tag=f"L={L} W={W}", route=route, split=(W == 8))
+
+
+@pytest.mark.parametrize("f,W,n,L,small", [
+    (F(5, 2), 8, 1 << 20, 16, True), (F(5, 2), 8, (1 << 20) + 4, 16, False),
+    (F(5, 2), 32, 1 << 18, 16, True), (F(5, 2), 32, (1 << 18) + 4, 16, False),
+    (F(5, 2), 64, 1 << 16, 16, True), (F(5, 2), 64, (1 << 16) + 4, 16, False),
+    (F(5, 2), 128, 2048, 16, True), (F(5, 2), 128, 2048, 15, False), (F(5, 2), 128, 1 << 17, 1024, True),
+    (F(5, 2), 1024, 256, 3, False), (F(5, 2), 1024, 256, 64, True), (F(5, 2), 16, 1 << 20, 4096, True),
+    (F(5, 2), 8, 1 << 18, 1, True), (F(5, 2), 8, (1 << 18) + 4, 1, False),
+    (F(4, 3), 12, 1 << 20, 16, True), (F(4, 3), 16, 3 << 18, 16, True), (F(4, 3), 16, (3 << 18) + 4, 16, False),
+    (F(4, 3), 16, 1 << 20, 4096, True),
+    (F(4, 3), 256, 4096, 16, True), (F(4, 3), 4096, 250, 2, True), (F(4, 3), 4097, 250, 2, False),
+], ids=str)
+def test_sync_small_set_rule(dev, f, W, n, L, small):
+    """Which default calls take the two launches of the small sets, on both
+    sides of each bound, told by what they leave in the workspace: those write
+    a word per unit of 256 elements and layer at its start, the one-pass route
+    tables behind its byte per element, two passes nothing."""
+    rng = np.random.default_rng(W + n)
+    cuts = np.sort(rng.choice(np.arange(1, n), L - 1, replace=False))
+    offs = np.concatenate([[0], cuts, [n]]).astype(np.int64)
+    ld = (n + 63) // 64 * 64
+    G = _values(rng, W, ld, offs, "normal")
+    ws = torch.full((A.aps_sync_workspace_bytes(n, L),), 0xA5, dtype=torch.uint8, device=dev)
+    out, se, mab, _ = A.aps_sync(torch.from_numpy(G).to(dev), n, torch.from_numpy(offs).to(dev), [f], workspace=ws)
+    touched = torch.nonzero(ws != 0xA5)
+    extent = int(touched.max()) + 1 if touched.numel() else 0
+    assert (0 < extent <= 4 * ((n + 255) // 256 + L)) == small, extent
+    o_se = O.layer_scales(O.layer_maxabs(G, n, offs), W, ofmt(f))
+    assert np.array_equal(se.cpu().numpy(), o_se)
+    o_out = O.sim_reduce(G, n, offs, o_se, ofmt(f))
+    g = out.cpu().numpy()
+    assert same_f32(g, o_out), first_diff(g, o_out)
