@@ -410,11 +410,15 @@ __global__ void k_sync_bookkeep(const uint32_t* __restrict__ maxabs, Layers ly, 
     int32_t th = 0;
     bool mixed = false;
     const int p0 = ly.fmt_idx ? ly.fmt_idx[i0] : 0;
-    for (int i = i0; i < ly.L && offset(i) < end; ++i) {
-        if (offset(i) == offset(i + 1)) continue;  // empty layer
-        int32_t r;
-        th = max(th, layer_th(i, r));
-        if (ly.fmt_idx && ly.fmt_idx[i] != p0) mixed = true;
+    int64_t lo = offset(i0);  // one read per layer: its start is where the last one ended
+    for (int i = i0; lo < end; ++i) {  // offsets[L] = n >= end
+        const int64_t hi = offset(i + 1);
+        if (lo < hi) {  // not an empty layer
+            int32_t r;
+            th = max(th, layer_th(i, r));
+            if (ly.fmt_idx && ly.fmt_idx[i] != p0) mixed = true;
+        }
+        lo = hi;
     }
     const bool listed = !mixed && (int32_t)cm < th;
     if (listed) ws.list[atomicAdd(ws.count, 1u)] = (int32_t)t;
