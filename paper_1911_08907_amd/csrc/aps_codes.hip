@@ -217,13 +217,13 @@ __global__ __launch_bounds__(BLOCK) void k_sim_reduce_codes(CodesArgs a, Layers 
                     const f4 v = {o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]};
                     *(f4*)(wbuf + lane * EPT + 4 * q) = v;
                 }
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_sync();
 #pragma unroll
                 for (int q = 0; q < EPT / 4; ++q) {
                     const f4 v = *(const f4*)(wbuf + 4 * lane + 256 * q);
                     __builtin_nontemporal_store(v, (f4*)(a.out + wbase + 4 * lane + 256 * q));
                 }
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_sync();
             }
             if (a.codes_out) {
                 const u4v v = {cw[0], cw[1], cw[2], cw[3]};

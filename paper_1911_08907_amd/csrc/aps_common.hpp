@@ -593,6 +593,17 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     return v;
 }
 
+// Between the lanes of one wave passing values through LDS: what any of them
+// wrote before is what any of them reads after.  A wave's LDS operations
+// complete in order, so it costs no instruction; the fences are for the
+// compiler, for which a lane that wrote a word and did not write it again might
+// else read its own value back.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Block-wide max of v (all threads call it), then one atomicMax if nonzero.
 __device__ __forceinline__ void block_max_atomic(uint32_t v, uint32_t* dst, uint32_t* red) {
     v = wave_max_u32(v);

@@ -30,12 +30,12 @@ __device__ __forceinline__ void layer_starts(const Layers& ly, const ChunkInfo& 
                                              uint32_t* mark, uint32_t pos[4]) {
     const int lane = threadIdx.x & 63;
     *(u4v*)(mark + 4 * lane) = u4v{0u, 0u, 0u, 0u};
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     for (int64_t i = ci.i0 + lane; i <= ci.i1; i += 64) {
         const int64_t lo = ly.offsets[i];
         if (lo > start && lo < end && ly.offsets[i + 1] > lo) mark[lo - start] = (uint32_t)(lo - start);
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     const u4v m = *(const u4v*)(mark + 4 * lane);
     pos[0] = m.x;
     pos[1] = max(m.y, pos[0]);
@@ -49,7 +49,7 @@ __device__ __forceinline__ void layer_starts(const Layers& ly, const ChunkInfo& 
     const uint32_t prev = (uint32_t)__shfl_up((int)before, 1, 64);
     if (lane > 0)
         for (int e = 0; e < 4; ++e) pos[e] = max(pos[e], prev);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
 }
 
 // Every unit's maximum magnitude per layer.
@@ -87,10 +87,10 @@ __global__ __launch_bounds__(BLOCK) void k_small_max(const float* __restrict__ G
     uint32_t pos[4];
     layer_starts(ly, ci, start, end, smark[wv], pos);
     *(u4v*)(smax[wv] + 4 * lane) = u4v{0u, 0u, 0u, 0u};
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     for (int e = 0; e < 4; ++e)
         if (m[e]) atomicMax(&smax[wv][pos[e]], m[e]);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     for (int64_t i = ci.i0 + lane; i <= ci.i1; i += 64) {
         const int64_t lo = max(ly.offsets[i], start), hi = min(ly.offsets[i + 1], end);
         if (lo < hi) part[u + i] = smax[wv][lo - start];
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(BLOCK) void k_small_sum(ReduceArgs a, Layers ly, Fm
                     }
                     sft[wv][lo - start] = r;
                 }
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_sync();
                 for (int e = 0; e < 4; ++e) ft[e] = sft[wv][pos[e]];
             }
             for (int e = 0; e < 4; ++e) F[e] = clamp_exp(ft[e]) + f.k;
