@@ -355,6 +355,12 @@ extern "C" int aps_sim_reduce_codes(const void* codes, int32_t W, int64_t ld, in
     // better than 16 per CU (ResNet-50, W = 64: 1-5-2 334 -> 307 us, 1-5-10
     // 639 -> 579 us; W = 8 the same)
     const dim3 grid((unsigned)grid_for(nchunks, 64));
+    // (16-bit codes decode so slowly without the hardware that a large set is
+    // worth 1-5-10's own launch: 1-5-10 and 1-5-7 in turn, one launch and two, us:
+    // 25.6 M W = 8 183 and 167, 3 M W = 64 276 and 262, 0.3 M W = 256 785 and 820)
+    if (ccls < 2 || (int64_t)W * n < ((int64_t)1 << 27))
+        one_form_per_variant(
+            pal, n_fmts, [](const FmtK& f) { return f.variant; }, [&](const FmtK& f) { return hw_of_codes(f, ccls); });
     unsigned vm = 0, hm = 0;  // variants of the entries without, and forms of those with, hardware codes
     for (int i = 0; i < n_fmts; ++i) {
         const int hw = hw_of_codes(pal.f[i], ccls);

@@ -1042,6 +1042,21 @@ static inline unsigned variant_mask(const Pal& pal, int32_t n_fmts) {
     return m;
 }
 
+// Entries of one kernel variant share a launch, and each hardware form is a
+// launch of its own.  Where the entries of a variant do not all take the same
+// form, none takes one: every launch walks all chunks and idles on the others'
+// (ResNet-50, 1-5-2 and 1-5-1 in turn: encode W = 1 107 us in two launches, 78 in
+// one, W = 8 220 and 204; the sum of codes, 3 M elements W = 3, 43 and 40).
+template <class Key, class Form>
+static inline void one_form_per_variant(Pal& pal, int32_t n_fmts, Key key, Form form) {
+    bool drop[APS_MAX_FORMATS] = {};
+    for (int i = 0; i < n_fmts; ++i)
+        for (int j = 0; j < n_fmts; ++j)
+            if (key(pal.f[i]) == key(pal.f[j]) && form(pal.f[i]) != form(pal.f[j])) drop[i] = true;
+    for (int i = 0; i < n_fmts; ++i)
+        if (drop[i]) pal.f[i].hw = HW_NONE;
+}
+
 }  // namespace aps
 
 namespace aps {

@@ -439,6 +439,8 @@ extern "C" int aps_sim_reduce_ex(const float* G, int32_t W, int64_t ld, int64_t 
     ReduceArgs a{G, out, (uint8_t*)codes_out, ld, W, flags, ccls, nullptr, nullptr};
     Order od{__builtin_ctz((unsigned)group), W / group};
     const int64_t nchunks = (n + CH - 1) / CH;
+    one_form_per_variant(
+        pal, n_fmts, [](const FmtK& f) { return f.variant; }, [](const FmtK& f) { return hw_of_chain(f); });
     unsigned vm = 0, hm = 0;  // variants of the entries without, and forms of those with, hardware chains
     for (int i = 0; i < n_fmts; ++i) {
         const int hw = hw_of_chain(pal.f[i]);

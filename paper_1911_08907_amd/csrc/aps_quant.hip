@@ -399,6 +399,8 @@ extern "C" int aps_quantize(const float* X, int32_t W, int64_t ld, int64_t n, co
     // 64 blocks per CU (ResNet-50 at W = 8: 0.223 -> 0.20 ms)
     const dim3 grid((unsigned)grid_for(nchunks, W < 64 ? 64 : BLOCKS_PER_CU));
     const int out = !codes ? QO_Q : (Q ? QO_BOTH : QO_CODES4 + ccls);
+    one_form_per_variant(
+        pal, n_fmts, [](const FmtK& f) { return cast_variant(f.variant); }, [&](const FmtK& f) { return hw_of_cast(f, out); });
     unsigned cm = 0, hm = 0;  // cast variants, and hardware forms, present
     for (int i = 0; i < n_fmts; ++i) {
         const int hw = hw_of_cast(pal.f[i], out);

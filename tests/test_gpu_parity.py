@@ -1095,3 +1095,31 @@ def test_ordered_reduce_by_hardware_chains(dev, f, acc):
                 ref = O.sim_reduce_ex(G, n, offs, se, [ofmt(p) for p in pal], ix, flags=flags, group=k, accumulator=acc)
                 g = out.cpu().numpy()
                 assert same_f32(g, ref), first_diff(g, ref)
+
+
+@pytest.mark.parametrize("pal", [[F(5, 2), F(5, 1)], [F(4, 3), F(4, 2), F(5, 2)], [F(5, 10), F(5, 7)], [F(5, 2), F(4, 3)],
+                                 [F(5, 2), F(5, 10), F(4, 3)]], ids=lambda p: "+".join(str(f) for f in p))
+def test_palettes_that_share_a_variant(dev, pal):
+    """Palettes of which one entry has a hardware form and another of the same
+    kernel variant has not, or has another (all then take the general one), and
+    one where each variant has a single form: casts, codes, their sum and
+    decode, and the ordered sum, chunks of one entry and chunks that mix them."""
+    rng = np.random.default_rng(zlib.crc32("+".join(str(f) for f in pal).encode()))
+    sizes = [int(v) for v in rng.choice([1, 17, 1023, 1024, 3000, 9000], 24)]
+    offs, n, ld = _layout(sizes)
+    fmt_idx = rng.integers(0, len(pal), len(sizes)).astype(np.uint8)
+    for W, kind in ((3, "special"), (8, "normal"), (5, "tiny")):
+        G = _values(rng, W, ld, offs, kind)
+        run_case(dev, G, n, offs, pal, fmt_idx, tag=f"W={W} {kind}")
+        if len({_code_cls(f.bits) for f in pal}) == 1:  # the codes alone
+            bits = max(f.bits for f in pal)
+            rb = _row_code_bytes(ld, bits)
+            codes = torch.zeros(W * rb, dtype=torch.uint8, device=dev)
+            A.aps_quantize(torch.from_numpy(G).to(dev), n, torch.from_numpy(offs).to(dev), None, pal,
+                           torch.from_numpy(fmt_idx).to(dev), codes=codes)
+            o_Q = O.quantize(G, n, offs, None, [ofmt(f) for f in pal], fmt_idx)
+            for w in range(W):
+                oc = O.pack_codes(o_Q[w, :n], offs, [ofmt(f) for f in pal], fmt_idx)
+                assert _codes_equal(codes.cpu().numpy()[w * rb:(w + 1) * rb], oc, n, bits, np.isnan(o_Q[w, :n])), (W, kind, w)
+        for acc in (A.APS_ACC_SEQUENTIAL, A.APS_ACC_KAHAN):
+            _run_ex(dev, G, n, offs, pal, fmt_idx, None, 1, acc, f"ring W={W} {kind} acc={acc}")
