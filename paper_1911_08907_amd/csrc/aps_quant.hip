@@ -240,19 +240,22 @@ __device__ __forceinline__ void deq_hw(const DeqRaw& r, float v[4]) {
     }
 }
 
-// Chunks a block has in flight at once: their loads are issued together, so
-// each wave waits for memory once per DEQ_GROUP chunks (the work per chunk
-// is 4 elements per thread, too little to cover a load's latency).
-constexpr int DEQ_GROUP = 8;
-
+// Chunks a block has in flight at once (GRP, a template argument): their loads
+// are issued together, so each wave waits for memory once per GRP chunks (the
+// work per chunk is 4 elements per thread, too little to cover a load's
+// latency).  Eight for codes, four for fp32 values, whose loads are four times
+// as wide, and where no block has more than four: past its last chunk a block
+// loads that one again.  With four and eight, us: fp32 4.3 M elements 11.3 and
+// 16.8, 18 M 27.0 and 29.4; 1-8-7 3 M 12.0 and 13.1; 1-5-2 25.6 M 29.6 and 28.1.
+//
 // Palettes all of 1-5-2, of 1-4-3 or of 1-5-10 decode by the hardware's
 // conversions (HW).  Other codes of up to 8 bits decode through a table in
 // LDS, one per palette entry (value of every code), filled once per block;
-// other 16-bit codes decode arithmetically.  A block walks its chunks in groups of DEQ_GROUP: the loads
+// other 16-bit codes decode arithmetically.  A block walks its chunks in groups: the loads
 // of the next group are issued before the current one is decoded and
 // stored, and the first group's before the table is filled, so each wave
 // has a group's loads in flight while it works.
-template <int IN, int HW>
+template <int IN, int HW, int GRP>
 __global__ __launch_bounds__(BLOCK) void k_dequantize(DeqArgs a, Layers ly, Pal pal) {
     constexpr bool TABLE = HW == HW_NONE && (IN == 1 || IN == 2);
     constexpr int NCODES = IN == 1 ? 16 : 256;
@@ -291,22 +294,22 @@ __global__ __launch_bounds__(BLOCK) void k_dequantize(DeqArgs a, Layers ly, Pal 
     }
     if (cb >= ce) return;  // uniform per block
     LayerCur cur{-1, 0};
-    ChunkInfo cis[DEQ_GROUP];
-    DeqRaw raw[DEQ_GROUP];
+    ChunkInfo cis[GRP];
+    DeqRaw raw[GRP];
     // the chunks' layers first (scalar loads, wave-uniform), then the group's
     // data loads, all in flight together
     auto issue = [&](int64_t c0) {
         // usually the whole group lies in one layer: one lookup for all of it
-        const int64_t gend = min(min(c0 + DEQ_GROUP, ce) * CH, ly.n);
+        const int64_t gend = min(min(c0 + GRP, ce) * CH, ly.n);
         const LayerCur at = cur;
         const ChunkInfo gi = chunk_layers(ly, c0 * CH, gend, cur);
         if (gi.i0 == gi.i1) {
 #pragma unroll
-            for (int g = 0; g < DEQ_GROUP; ++g) cis[g] = gi;
+            for (int g = 0; g < GRP; ++g) cis[g] = gi;
         } else {
             cur = at;  // chunk by chunk
 #pragma unroll
-            for (int g = 0; g < DEQ_GROUP; ++g) {
+            for (int g = 0; g < GRP; ++g) {
                 const int64_t c = c0 + g;
                 if (c >= ce) {
                     cis[g] = cis[g - 1];  // not used
@@ -316,14 +319,14 @@ __global__ __launch_bounds__(BLOCK) void k_dequantize(DeqArgs a, Layers ly, Pal 
             }
         }
 #pragma unroll
-        for (int g = 0; g < DEQ_GROUP; ++g) {
+        for (int g = 0; g < GRP; ++g) {
             const int64_t j = min(c0 + g, ce - 1) * CH + (int64_t)threadIdx.x * VEC;
             raw[g] = deq_load<IN, HW>(a, min(j, jlast));
         }
     };
     auto process = [&](int64_t c0, const ChunkInfo* gci, const DeqRaw* graw) {
 #pragma unroll
-        for (int g = 0; g < DEQ_GROUP; ++g) {
+        for (int g = 0; g < GRP; ++g) {
             const int64_t c = c0 + g;
             if (c >= ce) break;
             const int64_t start = c * CH;
@@ -359,19 +362,19 @@ __global__ __launch_bounds__(BLOCK) void k_dequantize(DeqArgs a, Layers ly, Pal 
     };
     issue(cb);
     setup();
-    const int64_t ngroups = (ce - cb + DEQ_GROUP - 1) / DEQ_GROUP;
+    const int64_t ngroups = (ce - cb + GRP - 1) / GRP;
     for (int64_t k = 0; k + 1 < ngroups; ++k) {
-        ChunkInfo cur_ci[DEQ_GROUP];
-        DeqRaw cur[DEQ_GROUP];
+        ChunkInfo cur_ci[GRP];
+        DeqRaw cur[GRP];
 #pragma unroll
-        for (int g = 0; g < DEQ_GROUP; ++g) {
+        for (int g = 0; g < GRP; ++g) {
             cur_ci[g] = cis[g];
             cur[g] = raw[g];
         }
-        issue(cb + (k + 1) * DEQ_GROUP);
-        process(cb + k * DEQ_GROUP, cur_ci, cur);
+        issue(cb + (k + 1) * GRP);
+        process(cb + k * GRP, cur_ci, cur);
     }
-    process(cb + (ngroups - 1) * DEQ_GROUP, cis, raw);
+    process(cb + (ngroups - 1) * GRP, cis, raw);
 }
 
 }  // namespace aps
@@ -456,7 +459,12 @@ extern "C" int aps_dequantize(const float* Q, const void* codes, int64_t n, cons
     int hw = pal.f[0].hw;  // the whole palette's, or none
     for (int i = 1; i < n_fmts; ++i)
         if (pal.f[i].hw != hw) hw = HW_NONE;
-#define APS_D(i, h) hipLaunchKernelGGL((k_dequantize<i, h>), grid, dim3(BLOCK), 0, s, a, ly, pal)
+    const bool few = in == 0 || nchunks <= 4 * (int64_t)grid.x;
+#define APS_D(i, h)                                                                                \
+    do {                                                                                           \
+        if (i == 0 || few) hipLaunchKernelGGL((k_dequantize<i, h, 4>), grid, dim3(BLOCK), 0, s, a, ly, pal); \
+        else hipLaunchKernelGGL((k_dequantize<i, (i == 0 ? 0 : h), (i == 0 ? 4 : 8)>), grid, dim3(BLOCK), 0, s, a, ly, pal);     \
+    } while (0)
     if (in == 0) APS_D(0, HW_NONE);
     else if (in == 1) APS_D(1, HW_NONE);
     else if (in == 2 && hw == HW_E5M2) APS_D(2, HW_E5M2);
@@ -467,6 +475,3 @@ extern "C" int aps_dequantize(const float* Q, const void* codes, int64_t n, cons
 #undef APS_D
     return launched();
 }
-
-// Instantiates only the product modes a variant can take: GP_FIT needs the
-// TOP or LOW class with m >= 1; INT-class formats (k = 0) are always scaled.
