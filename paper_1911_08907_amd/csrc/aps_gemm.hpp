@@ -261,14 +261,14 @@ __global__ __launch_bounds__(BLOCK) void k_lp_gemm(GemmArgs g, FmtK fi, FmtK fa)
     const int64_t n0 = (int64_t)blockIdx.x * D::GN;
     for (int64_t m0 = (int64_t)blockIdx.y * D::GM; m0 < g.M; m0 += (int64_t)gridDim.y * D::GM) {
         float s[TM][TN], c[TM][TN];
-        bool bad[TM][TN];
+        uint64_t bad[TM][TN];  // m = 0: the lanes of the wave whose chain met a NaN
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 s[i][j] = 0.0f;
                 c[i][j] = 0.0f;
-                bad[i][j] = false;
+                bad[i][j] = 0;
             }
         GemmLoads<D> ld;
         auto put = [&](int buf) {
@@ -294,10 +294,11 @@ __global__ __launch_bounds__(BLOCK) void k_lp_gemm(GemmArgs g, FmtK fi, FmtK fa)
                 for (int j = 0; j < TN; ++j) {
                     // exact fp32 product of two input-format values, cast to the accumulator
                     float p = 0.0f;
+                    bool nan = false;
                     if constexpr (PM == GP_LDEXP)
-                        p = quant<V>(a[i] * b[j], fa.k, fa, bad[i][j]);
+                        p = quant<V>(a[i] * b[j], fa.k, fa, nan);
                     else if constexpr (PM == GP_SCALED)
-                        p = quant_w<V>(a[i] * b[j], fa, bad[i][j]);
+                        p = quant_w<V>(a[i] * b[j], fa, nan);
                     else if constexpr (PM == GP_FIT)
                         p = quant_fit<V>(a[i] * b[j], fa);
                     else if constexpr (PM == GP_GRID || PM == GP_B7_GRID)
@@ -318,7 +319,14 @@ __global__ __launch_bounds__(BLOCK) void k_lp_gemm(GemmArgs g, FmtK fi, FmtK fa)
                             s[i][j] = rnd(FMA ? __builtin_fmaf(a[i], b[j], s[i][j]) : s[i][j] + p);
                         }
                     } else {
-                        chain_step<V, KAHAN>(s[i][j], c[i][j], p, fa, bad[i][j]);
+                        chain_step<V, KAHAN>(s[i][j], c[i][j], p, fa, nan);
+                    }
+                    if constexpr (VT<V>::m0) {
+                        // a wave's mask in scalar registers, due here: a flag per lane the
+                        // compiler tests after the unrolled steps, with every product and sum
+                        // of theirs held in registers
+                        bad[i][j] |= __ballot(nan);
+                        asm volatile("" : "+s"(bad[i][j]));
                     }
                 }
         };
@@ -380,7 +388,8 @@ __global__ __launch_bounds__(BLOCK) void k_lp_gemm(GemmArgs g, FmtK fi, FmtK fa)
             float* crow = g.C + m * g.ldc;
             float o[TN];
 #pragma unroll
-            for (int j = 0; j < TN; ++j) o[j] = __builtin_amdgcn_ldexpf(finish<V>(s[i][j], bad[i][j]), -fa.k);
+            for (int j = 0; j < TN; ++j)
+                o[j] = __builtin_amdgcn_ldexpf(finish<V>(s[i][j], (bad[i][j] >> (t & 63)) & 1u), -fa.k);
             const int64_t n = n0 + tx * TN;
             if (TN >= 4 && n + TN <= g.N) {
 #pragma unroll

@@ -1123,3 +1123,24 @@ def test_palettes_that_share_a_variant(dev, pal):
                 assert _codes_equal(codes.cpu().numpy()[w * rb:(w + 1) * rb], oc, n, bits, np.isnan(o_Q[w, :n])), (W, kind, w)
         for acc in (A.APS_ACC_SEQUENTIAL, A.APS_ACC_KAHAN):
             _run_ex(dev, G, n, offs, pal, fmt_idx, None, 1, acc, f"ring W={W} {kind} acc={acc}")
+
+
+@pytest.mark.parametrize("acc", [A.APS_ACC_SEQUENTIAL, A.APS_ACC_KAHAN])
+@pytest.mark.parametrize("fin,facc", [(F(5, 2), F(3, 0)), (F(5, 2), F(8, 0)), (F(3, 0), F(5, 0)), (F(3, 0), F(2, 0)), (F(8, 0), F(8, 0))], ids=str)
+def test_lp_gemm_nan_flags_of_mantissa_free_accumulators(dev, fin, facc, acc):
+    """NaN in single inputs, and INF - INF sums, in every lane and at k of
+    every position in a k-tile: an m = 0 accumulator has no NaN pattern that its
+    rounding keeps, so a chain's NaN is a flag of its own, one per output."""
+    rng = np.random.default_rng(fin.e * 100 + facc.e + acc)
+    for M, K, N in ((70, 150, 66), (33, 64, 200), (16, 3, 16)):
+        Am = (rng.standard_normal((M, K)) * 0.25).astype(np.float32)
+        Bm = (rng.standard_normal((K, N)) * 0.25).astype(np.float32)
+        for _ in range(min(12, M // 4)):
+            Am[rng.integers(M), rng.integers(K)] = np.nan
+        Am[rng.integers(M), 0] = np.inf
+        Bm[rng.integers(K), rng.integers(N)] = -np.inf
+        Bm[K - 1, N - 1] = np.nan
+        C = A.aps_lp_gemm(torch.from_numpy(Am).to(dev), torch.from_numpy(Bm).to(dev), fin, facc, acc).cpu().numpy()
+        o = O.lp_gemm(Am, Bm, ofmt(fin), ofmt(facc), acc)
+        assert np.isnan(o).any() and not np.isnan(o).all()
+        assert same_f32(C, o), first_diff(C, o)
