@@ -708,41 +708,70 @@ inline dim3 gemm_grid(const GemmArgs& g, int gm, int gn) {
     return dim3((unsigned)((g.N + gn - 1) / gn), (unsigned)std::min((g.M + gm - 1) / gm, 65535));
 }
 
-// The tiles of k_lp_gemm (outputs per thread).  Measured on MI355X, 1-5-2
-// into 1-8-7 plain and 1-4-3 into 1-8-7 Kahan, us:
-//                         4x4    2x2    1x2    1x1 | Kahan  4x4   2x2   1x2   1x1
-//   4096 x 4096 x 1024    934    937   1180   2060         3612  3613  3561  3461
-//   1024 x 1024 x 1024    108     82     91    146          278   251   239   238
-//   256 x 1000 x 2048     202     69     57     83          544   166   149   145
-//   64 x 64 x 4096        400    130     90     68         1068   308   177   115
+// The tiles of k_lp_gemm (outputs per thread).  Measured on MI355X, us, 1-5-2
+// inputs: into 1-8-7 plain, then with Kahan's chain into 1-8-7, 1-5-2 and 1-8-23:
+//                       4x4   2x2   1x2   1x1 |  4x4   2x2   1x1 |  4x4   2x2   1x1 |  4x4   2x2   1x1
+//   4096 x 4096 x 512   469   475   599  1041 | 1806  1788  1705 | 4643  4695  4925 |  634   700  1126
+//   1024 x 1024 x 1024  104    76    84   137 |  275   242   226 |  854   655   645 |  235   120   159
+//   256 x 1000 x 2048   202    67    52    77 |  541   157   129 | 1695   482   369 |  464   171   100
+//   4096 x 4096 x 8      16    27    55    73 |   33    38    76 |   78    91   166 |   23    39   116
+//   512 x 512 x 8       3.8   2.9   3.3   3.4 |  4.9   3.1   3.5 |  9.8   5.4   5.6 |  5.3   4.1   5.0
 // A plain chain has two to eight VALU instructions per product, so 1 x 1 is
 // bound by its two LDS reads per product and 2 x 2 is not; below three 2 x 2
 // blocks per CU smaller tiles spread the chains over more waves, down to
-// 1 x 1 where even its blocks do not outnumber the CUs.  Kahan's chain (eight
-// and more) hides the reads at 1 x 1, whose many waves hide the chain's
-// latency at every size.  4 x 4 only where an add is the fma alone (1-8-23).
+// 1 x 1 where even its blocks do not outnumber the CUs.  Kahan's chain hides
+// the reads at 1 x 1, whose many waves hide the chain's latency, where its adds
+// are one instruction (7 mantissa bits) or bound by fp64; on large products of
+// the other classes 1 x 1 costs 5 %, and where an add is the fma alone (1-8-23)
+// the reads bind it as they do a plain chain.  A block costs its launch and the
+// staging of a whole k-tile however small K is: below K = 64, the largest
+// k-tile, large products take 4 x 4 and k-tiles of 16, below 32 the others 2 x 2.
+enum GemmTiles { GT_4X4, GT_2X2, GT_1X2, GT_1X1 };
+
+// Outputs computed with tiles of gm x gn, the padding of the edges included.
+inline int64_t gemm_padded(const GemmArgs& g, int64_t gm, int64_t gn) {
+    return (g.M + gm - 1) / gm * gm * ((g.N + gn - 1) / gn * gn);
+}
+
+inline GemmTiles gemm_tiles(const GemmArgs& g, bool kahan, bool exact, bool hides) {
+    const auto blocks = [&](int64_t gt) { return gemm_padded(g, gt, gt) / (gt * gt); };
+    // whether tiles of gt pad a narrow product to at most `most` times what those of
+    // `than` do (2^20 x 4 x 16 into 1-8-7 with Kahan's chain: 219 us at 4 x 4, 96 at
+    // 1 x 1; 1-8-23 gains more by 4 x 4, and at the smallest K by 2 x 2, than that costs)
+    const auto fits = [&](int64_t gt, int64_t than, double most) {
+        return (double)gemm_padded(g, gt, gt) <= most * (double)gemm_padded(g, than, than);
+    };
+    const bool fit4 = fits(64, kahan ? 16 : 32, exact ? 1.6 : 1.25);
+    const bool fit2 = !kahan || fits(32, 16, exact && g.K < 16 ? 2.0 : (g.K < 64 ? 1.25 : 1.05));
+    if (exact && blocks(64) >= 512 && (fit4 || !kahan)) return GT_4X4;  // an add is the fma alone
+    if (g.K < 64 && blocks(64) >= (g.K < 32 ? 512 : 1024) && fit4) return GT_4X4;
+    if (g.K < 32 && fit2) return blocks(16) > 256 ? GT_2X2 : GT_1X1;
+    if (kahan) {
+        const int64_t least = g.K < 64 || exact ? 768 : (hides ? INT64_MAX : 2048);
+        return fit2 && blocks(32) >= least ? GT_2X2 : GT_1X1;
+    }
+    if (blocks(32) >= 768) return GT_2X2;
+    return blocks(16) > 256 ? GT_1X2 : GT_1X1;
+}
+
 template <int V, int PM, int VI = -1>
 static void launch_gemm(bool kahan, hipStream_t s, const GemmArgs& g, const FmtK& fi, const FmtK& fa) {
-    const auto blocks = [&](int64_t gt) { return ((g.M + gt - 1) / gt) * ((g.N + gt - 1) / gt); };
 #define APS_GL(K, TM, TN, GK)                                                                                     \
     hipLaunchKernelGGL((k_lp_gemm<V, K, PM, VI, TM, TN, GK>), gemm_grid(g, 16 * TM, 16 * TN), dim3(BLOCK), 0, s, g, \
                        fi, fa)
+    // whether Kahan's chain hides the operand reads: 7 mantissa bits, fp64 adds
+    constexpr bool hides = PM >= GP_B7_GRID || VT<V>::acc == ACC_F64;
+    const GemmTiles tiles = gemm_tiles(g, kahan, VT<V>::acc == ACC_EXACT, hides);
     if (kahan) {
-        APS_GL(true, 1, 1, 64);
-        return;
+        if (tiles == GT_4X4) APS_GL(true, 4, 4, 16);
+        else if (tiles == GT_2X2) APS_GL(true, 2, 2, 32);
+        else APS_GL(true, 1, 1, 64);
+    } else {
+        if (tiles == GT_4X4) APS_GL(false, 4, 4, 16);
+        else if (tiles == GT_2X2) APS_GL(false, 2, 2, 32);
+        else if (tiles == GT_1X2) APS_GL(false, 1, 2, 64);
+        else APS_GL(false, 1, 1, 64);
     }
-    if constexpr (V == V_INT_EXACT) {
-        if (blocks(64) >= 512) {
-            APS_GL(false, 4, 4, 16);
-            return;
-        }
-    }
-    if (blocks(32) >= 768)
-        APS_GL(false, 2, 2, 32);
-    else if (blocks(16) > 256)
-        APS_GL(false, 1, 2, 64);
-    else
-        APS_GL(false, 1, 1, 64);
 #undef APS_GL
 }
 

@@ -1144,3 +1144,27 @@ def test_lp_gemm_nan_flags_of_mantissa_free_accumulators(dev, fin, facc, acc):
         o = O.lp_gemm(Am, Bm, ofmt(fin), ofmt(facc), acc)
         assert np.isnan(o).any() and not np.isnan(o).all()
         assert same_f32(C, o), first_diff(C, o)
+
+
+@pytest.mark.parametrize("acc", [A.APS_ACC_SEQUENTIAL, A.APS_ACC_KAHAN])
+@pytest.mark.parametrize("fin,facc", [(F(5, 2), F(8, 7)), (F(5, 2), F(5, 7)), (F(5, 2), F(8, 23)), (F(4, 3), F(5, 5)),
+                                      (F(8, 7), F(8, 7)), (F(5, 2), F(5, 12)), (F(5, 2), F(3, 0))], ids=str)
+def test_lp_gemm_tiles_by_k_and_size(dev, fin, facc, acc):
+    """Each tile of the emulated accumulators on both sides of the rule's
+    lines (K below and from 32 and 64; 512 and 1024 tiles of 64 x 64, 768 and
+    2048 of 32 x 32, 256 of 16 x 16; narrow sides), sizes that end inside a
+    tile and K inside a k-tile, on sampled rows and columns."""
+    rng = np.random.default_rng(fin.e * 1000 + facc.e * 10 + facc.m + acc)
+    for M, N, K in ((2050, 2046, 1), (2050, 2046, 19), (2050, 2046, 63), (2050, 2046, 64), (1028, 1019, 31),
+                    (1028, 1019, 33), (1028, 1019, 70), (1450, 1451, 65), (130, 1030, 7), (130, 1030, 66), (250, 241, 40),
+                    (6, 9000, 4), (9000, 33, 16), (40000, 5, 20)):
+        Am = rng.standard_normal((M, K)).astype(np.float32)
+        Bm = (rng.standard_normal((K, N)) * 0.02).astype(np.float32)
+        Am[M - 1, K // 2] = np.inf
+        log("M", M, "N", N, "K", K)
+        C = A.aps_lp_gemm(torch.from_numpy(Am).to(dev), torch.from_numpy(Bm).to(dev), fin, facc, acc).cpu().numpy()
+        rows = np.unique(np.concatenate([np.minimum([0, 1, 63, 64, M - 2], M - 1), [M - 1], rng.integers(0, M, 20)]))
+        cols = np.unique(np.concatenate([np.minimum([0, 3, 63, 64, N - 2], N - 1), [N - 1], rng.integers(0, N, 60)]))
+        o = O.lp_gemm(Am[rows], np.ascontiguousarray(Bm[:, cols]), ofmt(fin), ofmt(facc), acc)
+        g = np.ascontiguousarray(C[np.ix_(rows, cols)])
+        assert same_f32(g, o), first_diff(g, o)
