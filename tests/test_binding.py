@@ -46,3 +46,15 @@ def test_every_compute_call_is_covered():
     compute = [nm for nm in A.EXPORTS if nm not in ("aps_format_supported", "aps_sync_workspace_bytes",
                                                      "aps_sync_route", "aps_strerror")]
     assert sorted(compute) == sorted(nm for nm in CALLS if nm != "aps_step")
+
+
+def test_current_stream_with_and_without_torchs_raw_handle(monkeypatch):
+    """The current stream's handle comes from torch's raw accessor where this
+    torch has it, and through a Stream object where it has not."""
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 7 + device, raising=False)
+    assert A._stream(None) == 7
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: type("S", (), {"cuda_stream": 1234})())
+    assert A._stream(None) == 1234
+    assert A._stream(5) == 5
