@@ -836,8 +836,10 @@ def test_lp_gemm_input_cast_rounding_cases(dev, fin, facc):
 @pytest.mark.parametrize("fin,facc", [(F(5, 2), F(5, 10)), (F(4, 3), F(5, 2))], ids=["half", "emulated"])
 @pytest.mark.parametrize("M,N", [(1 << 22, 3), (2, 1 << 22)])
 def test_lp_gemm_largest_dimensions(dev, M, N, fin, facc):
-    """M or N at APS_MAX_GEMM_DIM = 2^22: 65536 tiles along one dimension,
-    in both GEMM kernels (half-precision accumulator, and the emulated one)."""
+    """M or N at APS_MAX_GEMM_DIM = 2^22: 131072 tiles of 32 x 32 along one
+    dimension, in both GEMM kernels (half-precision accumulator, and the
+    emulated one); along M more than a grid has rows of blocks, so that a block
+    takes several."""
     rng = np.random.default_rng(977 + M % 7)
     Am, Bm = _gemm_inputs(rng, M, N, 2, fin)
     got = A.aps_lp_gemm(torch.from_numpy(Am).to(dev), torch.from_numpy(Bm).to(dev), fin, facc)
@@ -1048,10 +1050,12 @@ def test_codes_by_hardware_conversion(dev, f):
 
 @pytest.mark.parametrize("L", [1, 63, 64, 65, 200, 4096, 4200])
 def test_layer_lookup_over_many_layers(dev, L):
-    """The layers' lookup by 64 offsets at a time: layer counts around one, two
-    and three rounds of it, runs of empty layers at the start, in the middle
-    and at the end, and chunks that start inside, at the start and at the end
-    of a layer; a quarter of the layers in another format."""
+    """The layers' lookup of the casts, sums and decodes (a search for a block's
+    first chunk, then a walk): layer counts around powers of 64, runs of empty
+    layers at the start, in the middle and at the end, and chunks that start
+    inside, at the start and at the end of a layer; a quarter of the layers in
+    another format.  (The lookup by 64 offsets at a time is the one-pass route's:
+    test_sync_over_many_layers.)"""
     rng = np.random.default_rng(1500 + L)
     sizes = rng.choice([0, 0, 1, 3, 40, 700], L)
     sizes[: L // 8] = 0
@@ -1168,3 +1172,31 @@ def test_lp_gemm_tiles_by_k_and_size(dev, fin, facc, acc):
         o = O.lp_gemm(Am[rows], np.ascontiguousarray(Bm[:, cols]), ofmt(fin), ofmt(facc), acc)
         g = np.ascontiguousarray(C[np.ix_(rows, cols)])
         assert same_f32(g, o), first_diff(g, o)
+
+
+@pytest.mark.parametrize("acc", [A.APS_ACC_SEQUENTIAL, A.APS_ACC_KAHAN])
+def test_lp_gemm_half_product_test_off_and_on(dev, acc):
+    """1-5-2 into half at sizes of the tiles that test whether a k-step's
+    products are all halves: stretches of k-tiles whose products mostly are not
+    (the test goes off and is tried again every eighth tile), then are, then
+    are not, then are, with a quarter of the rows, those of one wave, the other
+    way round; K ends inside a k-tile.  Sampled rows and columns."""
+    rng = np.random.default_rng(1900 + acc)
+    M, N, K = 3600, 3500, 16 * 46 + 5
+    fine = np.concatenate([np.full(16 * t, v) for t, v in ((11, True), (12, False), (13, True), (10, False))]
+                          + [np.full(5, True)])
+    other = (np.arange(M) // 32) % 4 == 1
+    mant = lambda *shape: rng.choice([-1.75, -1.25, -1.0, 1.0, 1.5, 1.75], shape)  # noqa: E731
+    Am = (mant(M, K) * np.where(fine[None, :] ^ other[:, None], 2.0 ** -13, 0.25)).astype(np.float32)
+    Bm = (mant(K, N) * 2.0 ** rng.integers(-12, -9, (K, 1))).astype(np.float32)
+    log("half product test, acc", acc)
+    got = A.aps_lp_gemm(torch.from_numpy(Am).to(dev), torch.from_numpy(Bm).to(dev), F(5, 2), F(5, 10), acc)
+    torch.cuda.synchronize()
+    g = got.cpu().numpy()
+    rows = np.unique(np.concatenate([[0, 31, 32, 63, 64, 127, 128, M - 1], rng.integers(0, M, 12)]))
+    cols = np.unique(np.concatenate([[0, 63, 64, 127, 128, N - 1], rng.integers(0, N, 12)]))
+    ref = O.lp_gemm(Am[rows], Bm, O.Format(5, 2), O.Format(5, 10), acc)
+    assert same_f32(g[rows], ref), first_diff(g[rows], ref)
+    ref = O.lp_gemm(Am, np.ascontiguousarray(Bm[:, cols]), O.Format(5, 2), O.Format(5, 10), acc)
+    gc = np.ascontiguousarray(g[:, cols])
+    assert same_f32(gc, ref), first_diff(gc, ref)
