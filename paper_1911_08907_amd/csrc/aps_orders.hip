@@ -280,13 +280,14 @@ __device__ __forceinline__ void ex_chunk(const ReduceArgs& a, const Layers& ly, 
 constexpr bool ex_m0(int V) { return V == V_INT_M0 || V == V_TOP_M0 || V == V_LOW_M0; }
 
 // Waves per SIMD asked of an instance: four (at most 128 registers) where that
-// costs no scratch or little: 1-5-2 and the fp32 chains fit, wide Kahan chains
-// (fp64 adds) beside a crossing copy spill 17 registers and gain all the same.
-// Without a crossing copy those are left to the compiler (134 to 137 registers),
-// as are Kahan's m = 0 chains (152 to 154), three waves each: held to 128 the
-// latter spill 46, in the row walk too.
+// costs no scratch or little: 1-5-2 and the fp32 chains fit, Kahan's chains of
+// the GEN formats spill 7 registers (12 beside a crossing copy) and wide ones
+// (fp64 adds) 17 beside one, and gain all the same.  Without a crossing copy the
+// wide ones are left to the compiler (137 registers), as are Kahan's m = 0
+// chains (152 to 154), three waves each: held to 128 the latter spill 46, in
+// the row walk too.
 constexpr int ex_waves(int V, bool KAHAN, bool CROSS) {
-    const bool wide = V == V_INT_F64 || V == V_TOP_F64 || V == V_LOW_F64 || V == V_GEN;
+    const bool wide = V == V_INT_F64 || V == V_TOP_F64 || V == V_LOW_F64;
     return KAHAN && (ex_m0(V) || (wide && !CROSS)) ? 1 : 4;
 }
 
