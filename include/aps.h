@@ -248,13 +248,12 @@ int aps_sync_route(int32_t W, int64_t n, const aps_format* fmts, int32_t n_fmts,
  * fmt_idx, or one palette entry), sets that stay in the caches run as two
  * launches where that was measured faster than their route: the maxima per
  * 256 elements and layer, then the exponents and the scaled sums.  They are
- * those of at most 2^20 elements, and at most 2^18 per layer on the mean,
- * with, where the route below would be the one-pass one, W <= 64 and
- * W * n <= 2^23 (W = 64: 2^22), and where it would be two passes, W <= 4096 and
- * W * n <= 3 * 2^22; with max(4, W / 16) layers and more per 1024 elements,
- * W * n <= 2^24 in both (two passes: W <= 4096).  aps_sync_route, which knows
- * neither the layers nor the passes, names the route that such a set takes with
- * a route bit or in separate passes.
+ * those of at most 2^20 elements, at most 3 * 2^17 per layer on the mean, and
+ * at most 2^24 element-workers, with, where the route below would be two
+ * passes, W <= 4096, and where it would be the one-pass one, max(4, W / 16)
+ * layers and more per 1024 elements, or W <= 64 and W * n <= 2^23 (W = 64:
+ * 2^22).  aps_sync_route, which knows neither the layers nor the passes, names
+ * the route that such a set takes with a route bit or in separate passes.
  *
  * Route choice: APS_SYNC_TWO_PASS and APS_SYNC_GUESS force their routes;
  * APS_SYNC_ONE_PASS takes the one-pass route wherever it applies (else two

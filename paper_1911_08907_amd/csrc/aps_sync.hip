@@ -792,30 +792,30 @@ static int sync_route(int32_t W, int64_t n, const Pal& pal, int32_t n_fmts, uint
 // each unit of the second reads its layer's unit maxima, ever more of them as
 // layers grow (of which the host knows the mean).  The routes cost about 1.5 us
 // more for every layer that ends inside a chunk.  So: n at most 2^20, n / L at
-// most 2^18, and against
+// most 3 * 2^17, and against
 //   the one-pass route, which walks the rows once: W at most 64 with W * n at
-//     most 2^23 (W = 64: 2^22), or max(4, W / 16) layers per chunk;
-//   two passes: W at most 4096 with W * n at most 3 * 2^22, or 2^24 with that
-//     many layers.
+//     most 2^23 (W = 64: 2^22), or max(4, W / 16) layers per chunk and 2^24;
+//   two passes: W at most 4096 with W * n at most 2^24.
 // Measured on MI355X, us per call in a graph, the route's launches and these,
 // d: layers per chunk:
 //   one-pass, 1-5-2, L = 16: W = 2 n = 2^20 23 and 12; W = 8 n = 2^20 25 and 14;
 //     W = 32 n = 2^18 17.2 and 13.4, 2^19 22.9 and 26.6; W = 64 n = 2^16 18.6
-//     and 17.3, 2^18 22.7 and 25.2.  L = 1: W = 8 n = 2^20 23 and 26, W = 16
-//     n = 2^18 13.9 and 12.0, W = 64 n = 2^17 18.1 and 18.9.  n = 2^14: W = 128
+//     and 17.3, 2^18 22.7 and 25.2.  L = 1: W = 8 n = 272474 12.7 and 11.4, 2^19
+//     16.0 and 16.0, W = 16 n = 2^18 13.9 and 12.0, W = 64 n = 2^17 18.1 and 18.9.  n = 2^14: W = 128
 //     d = 1 28 and 28, d = 8 41 and 30; W = 256 d = 4 46 and 51, d = 16 63 and
 //     53; W = 512 d = 16 91 and 101, d = 32 111 and 101; W = 1024 d = 1 126 and
 //     204, d = 64 203 and 206
 //   two passes, 1-4-3, L = 16: W = 8 n = 2^20 25 and 13; W = 13 n = 2^20 30 and
-//     24; W = 256 n = 2^14 55 and 50; W = 4096 n = 2^11 815 and 814; W = 8192
-//     n = 2^10 1511 and 1703.  L = 200: W = 16 n = 2^20 27.5 and 28.8.  L = 1:
-//     W = 8 n = 2^20 23 and 25, W = 40 n = 2^17.7 18.0 and 18.1
+//     24; W = 64 n = 2^18 26.7 and 25.0; W = 256 n = 2^14 55 and 50; W = 4096
+//     n = 2^11 815 and 814; W = 8192 n = 2^10 1511 and 1703.  L = 200: W = 40
+//     n = 2^18.7 28.1 and 27.4, W = 16 n = 2^20 27.5 and 28.8.  L = 1: W = 8
+//     n = 2^20 23 and 25, W = 40 n = 2^18.7 26 and 32
 static bool small_set(int32_t W, int64_t n, int32_t L, int route) {
-    if (n > ((int64_t)1 << 20) || n > ((int64_t)L << 18)) return false;
+    if (n > ((int64_t)1 << 20) || n > (int64_t)L * (3 << 17)) return false;
     const int64_t work = (int64_t)W * n, nchunks = (n + CH - 1) / CH;
-    const bool many = L >= nchunks * std::max(4, W / 16) && work <= ((int64_t)1 << 24);
-    if (route == APS_SYNC_ROUTE_ONE_PASS) return many || (W <= 64 && work <= ((int64_t)1 << (W > 32 ? 22 : 23)));
-    return W <= 4096 && (many || work <= ((int64_t)3 << 22));
+    if (work > ((int64_t)1 << 24)) return false;
+    if (route != APS_SYNC_ROUTE_ONE_PASS) return W <= 4096;
+    return L >= nchunks * std::max(4, W / 16) || (W <= 64 && work <= ((int64_t)1 << (W > 32 ? 22 : 23)));
 }
 
 static constexpr uint32_t ROUTE_BITS = APS_SYNC_ONE_PASS | APS_SYNC_TWO_PASS | APS_SYNC_GUESS;

@@ -688,9 +688,9 @@ def test_sync_over_many_layers(dev, L):
     (F(5, 2), 64, 1 << 16, 16, True), (F(5, 2), 64, (1 << 16) + 4, 16, False),
     (F(5, 2), 128, 2048, 16, True), (F(5, 2), 128, 2048, 15, False), (F(5, 2), 128, 1 << 17, 1024, True),
     (F(5, 2), 1024, 256, 3, False), (F(5, 2), 1024, 256, 64, True), (F(5, 2), 16, 1 << 20, 4096, True),
-    (F(5, 2), 8, 1 << 18, 1, True), (F(5, 2), 8, (1 << 18) + 4, 1, False),
-    (F(4, 3), 12, 1 << 20, 16, True), (F(4, 3), 16, 3 << 18, 16, True), (F(4, 3), 16, (3 << 18) + 4, 16, False),
-    (F(4, 3), 16, 1 << 20, 4096, True),
+    (F(5, 2), 8, 3 << 17, 1, True), (F(5, 2), 8, (3 << 17) + 4, 1, False),
+    (F(4, 3), 12, 1 << 20, 16, True), (F(4, 3), 16, 1 << 20, 16, True), (F(4, 3), 17, 1 << 20, 16, False),
+    (F(4, 3), 8, (3 << 18) + 4, 2, False), (F(4, 3), 16, 1 << 20, 4096, True),
     (F(4, 3), 256, 4096, 16, True), (F(4, 3), 4096, 250, 2, True), (F(4, 3), 4097, 250, 2, False),
 ], ids=str)
 def test_sync_small_set_rule(dev, f, W, n, L, small):
