@@ -147,20 +147,12 @@ def _ptr(t):
     return t.data_ptr()
 
 
-def _current_stream(device: int) -> int:
-    """The hipStream_t of torch's current stream on a device: by the binding
-    that torch's own compiled code uses, where this torch has it, else through
-    a Stream object."""
-    import torch
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    return torch.cuda.current_stream(device).cuda_stream if raw is None else raw(device)
-
-
 def _stream(stream, dev=None):
     """The hipStream_t to launch on: the given stream, or torch's current
     stream.  The library launches on the current device, so the arrays'
     device must be the current one (and a torch stream's device)."""
     import torch
+    cur = None
     if dev is not None and dev.type == "cuda":
         cur = torch.cuda.current_device()
         if (dev.index if dev.index is not None else cur) != cur:
@@ -168,7 +160,11 @@ def _stream(stream, dev=None):
         if stream is not None and not isinstance(stream, int) and stream.device != torch.device("cuda", cur):
             raise ValueError(f"the stream is on {stream.device}, the arrays on {dev}")
     if stream is None:
-        return _current_stream(torch.cuda.current_device())
+        if cur is None:
+            cur = torch.cuda.current_device()
+        # the accessor that torch's own compiled code uses; not public, so not relied on
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        return raw(cur) if raw is not None else torch.cuda.current_stream(cur).cuda_stream
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
