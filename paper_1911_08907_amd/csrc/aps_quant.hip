@@ -459,13 +459,14 @@ extern "C" int aps_dequantize(const float* Q, const void* codes, int64_t n, cons
     int hw = pal.f[0].hw;  // the whole palette's, or none
     for (int i = 1; i < n_fmts; ++i)
         if (pal.f[i].hw != hw) hw = HW_NONE;
-    const bool few = in == 0 || nchunks <= 4 * (int64_t)grid.x;
-#define APS_D(i, h)                                                                                \
-    do {                                                                                           \
-        if (i == 0 || few) hipLaunchKernelGGL((k_dequantize<i, h, 4>), grid, dim3(BLOCK), 0, s, a, ly, pal); \
-        else hipLaunchKernelGGL((k_dequantize<i, (i == 0 ? 0 : h), (i == 0 ? 4 : 8)>), grid, dim3(BLOCK), 0, s, a, ly, pal);     \
+    const bool few = nchunks <= 4 * (int64_t)grid.x;
+#define APS_DG(i, h, grp) hipLaunchKernelGGL((k_dequantize<i, h, grp>), grid, dim3(BLOCK), 0, s, a, ly, pal)
+#define APS_D(i, h)                 \
+    do {                            \
+        if (few) APS_DG(i, h, 4);   \
+        else APS_DG(i, h, 8);       \
     } while (0)
-    if (in == 0) APS_D(0, HW_NONE);
+    if (in == 0) APS_DG(0, HW_NONE, 4);
     else if (in == 1) APS_D(1, HW_NONE);
     else if (in == 2 && hw == HW_E5M2) APS_D(2, HW_E5M2);
     else if (in == 2 && hw == HW_E4M3) APS_D(2, HW_E4M3);
@@ -473,5 +474,6 @@ extern "C" int aps_dequantize(const float* Q, const void* codes, int64_t n, cons
     else if (hw == HW_HALF) APS_D(3, HW_HALF);
     else APS_D(3, HW_NONE);
 #undef APS_D
+#undef APS_DG
     return launched();
 }
